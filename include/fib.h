@@ -359,10 +359,10 @@ int fib_mlp_gradient(fib_mlp_t* net, const float* X, const float* T, int64_t B, 
 
 /* fib_mlp_gradient for callers that cannot allocate device memory (code
  * under HIP graph capture, tight training loops, harnesses that forbid
- * allocation): the same kernels and the same result, bit for bit, with the
- * per-chunk partial gradients and losses in a fixed 16 MiB array of the
- * library's code object on the network's device instead of memory the
- * network allocates when a batch grows.  Allocates nothing and calls no
+ * allocation): the same kernels and the same result, bit for bit, with
+ * their work space in a fixed 32 MiB array of the library's code object on
+ * the network's device instead of memory the network allocates when a batch
+ * grows.  Allocates nothing and calls no
  * allocating routine.  Limit: ceil(B / 32) (n_params + 1) <= 2^22 floats
  * (B <= 4288 for the 31289-parameter ST57 network, 14944 for the 8964-
  * parameter Hodgkin-Huxley one); larger batches return FIB_EINVAL.  The

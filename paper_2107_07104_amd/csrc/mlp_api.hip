@@ -24,20 +24,23 @@ struct fib_mlp {
   float* d_m = nullptr;       // Adam first moment
   float* d_v = nullptr;       // Adam second moment
   float* d_grad = nullptr;
-  float* d_part = nullptr;    // per-chunk partial gradients
-  float* d_loss_part = nullptr;
-  int64_t part_chunks = 0;
+  void* d_frags = nullptr;    // BF16 operand fragments of d_params, always current
+  float* d_work = nullptr;    // work space of the gradient
+  int work_chunks = 0;        // chunks it holds
   int64_t t = 0;              // Adam step count
 };
 
-// Scratch of fib_mlp_gradient_noalloc: the per-chunk partial gradients and
-// losses, in a fixed array of every device's code object instead of memory
-// allocated per call.  The array's name is a host-side stand-in: host code
-// uses only the device address that hipGetSymbolAddress returns, looked up
-// once per device with that device current (at fib_mlp_create) and kept in
-// g_scratch below.  Every call on a device shares that device's array.
-static constexpr int64_t kScratchFloats = (int64_t)1 << 22;  // 16 MiB per device
-static __device__ __align__(256) float scratch[kScratchFloats];
+// Scratch of fib_mlp_gradient_noalloc: the gradient's work space, in a fixed
+// array of every device's code object instead of memory allocated
+// per call.  The array's name is a host-side stand-in: host code uses only
+// the device address that hipGetSymbolAddress returns, looked up once per
+// device with that device current (at fib_mlp_create) and kept in g_scratch
+// below.  Every call on a device shares that device's array.
+static __device__ __align__(256) float scratch[fib::kScratchFloats];
+
+// Batches fib_mlp_gradient_noalloc takes: ceil(B / 32) (n_params + 1) floats
+// at most.
+static constexpr int64_t kNoallocFloats = (int64_t)1 << 22;
 
 namespace fib {
 const MlpShape& mlp_shape(const fib_mlp* n) { return n->shape; }
@@ -85,18 +88,30 @@ float* scratch_of(int dev) {
   return g_scratch[dev];
 }
 
-int ensure_parts(fib_mlp* n, int64_t chunks) {
-  if (chunks <= n->part_chunks) return FIB_OK;
+// LDS of a chunk's activations, pre-activations and two gradient blocks in
+// FP32: the network widths this library takes are those for which it fits a
+// workgroup (the kernels' own LDS is smaller, whatever the widths).
+size_t chunk_fp32_bytes(const fib::MlpShape& s) {
+  int64_t f = 0, pmax = 0;
+  for (int l = 0; l <= s.L; ++l) {
+    f += s.pad[l] * (l > 0 && l < s.L ? 2 : 1);
+    pmax = std::max<int64_t>(pmax, s.pad[l]);
+  }
+  return sizeof(float) * fib::kChunk * (size_t)(f + 2 * pmax);
+}
+
+// Work space for passes of `chunks` chunks; it grows with the largest batch,
+// up to one pass.
+int ensure_work(fib_mlp* n, int chunks) {
+  if (chunks <= n->work_chunks) return FIB_OK;
   (void)hipStreamSynchronize(n->stream);
-  (void)hipFree(n->d_part);
-  (void)hipFree(n->d_loss_part);
-  n->d_part = nullptr;
-  n->d_loss_part = nullptr;
-  n->part_chunks = 0;
-  if (hipMalloc(&n->d_part, sizeof(float) * (size_t)chunks * n->shape.n_params) != hipSuccess ||
-      hipMalloc(&n->d_loss_part, sizeof(float) * (size_t)chunks) != hipSuccess)
-    return mfail(FIB_ENOMEM, "device allocation of %lld gradient chunks failed", (long long)chunks);
-  n->part_chunks = chunks;
+  (void)hipFree(n->d_work);
+  n->d_work = nullptr;
+  n->work_chunks = 0;
+  if (hipMalloc(&n->d_work, sizeof(float) * (size_t)chunks * fib::mlp_chunk_floats(n->shape)) !=
+      hipSuccess)
+    return mfail(FIB_ENOMEM, "device allocation of %d gradient chunks failed", chunks);
+  n->work_chunks = chunks;
   return FIB_OK;
 }
 
@@ -128,11 +143,24 @@ int fib_mlp_create(int32_t n_layers, const int32_t* sizes, int32_t activation, v
     off += s.size[l];
   }
   s.n_params = (int)off;
+  for (int l = 1; l <= n_layers; ++l) {
+    s.f_off[l] = s.n_frag;
+    s.n_frag += s.pad[l] * s.pad[l - 1];
+    s.r_off[l] = s.n_frag;
+    if (l > 1) s.n_frag += s.pad[l] * s.pad[l - 1];
+    const int ib = (s.size[l - 1] + 15) / 16, ob = (s.size[l] + 15) / 16;
+    s.a_ops[l] = s.n_ops;
+    s.d_ops[l] = s.n_ops + ib;
+    s.n_ops += ib + ob;
+    s.n_tiles += ob * ib;
+    s.bias_off[l] = s.n_bias;
+    s.n_bias += s.size[l];
+  }
   hipDeviceProp_t prop;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
     return mfail(FIB_EHIP, "no HIP device");
-  if (fib::mlp_train_lds_bytes(s) > prop.sharedMemPerBlock)
+  if (chunk_fp32_bytes(s) > prop.sharedMemPerBlock)
     return mfail(FIB_EUNSUPPORTED, "network too wide for one workgroup's LDS");
   if (int rc = scratch_setup(dev)) return rc;
   fib_mlp* n = new (std::nothrow) fib_mlp();
@@ -142,12 +170,14 @@ int fib_mlp_create(int32_t n_layers, const int32_t* sizes, int32_t activation, v
   n->device = dev;
   const size_t bytes = sizeof(float) * (size_t)s.n_params;
   if (hipMalloc(&n->d_params, bytes) != hipSuccess || hipMalloc(&n->d_m, bytes) != hipSuccess ||
-      hipMalloc(&n->d_v, bytes) != hipSuccess || hipMalloc(&n->d_grad, bytes) != hipSuccess) {
+      hipMalloc(&n->d_v, bytes) != hipSuccess || hipMalloc(&n->d_grad, bytes) != hipSuccess ||
+      hipMalloc(&n->d_frags, 2 * (size_t)s.n_frag) != hipSuccess) {
     fib_mlp_destroy(n);
     return mfail(FIB_ENOMEM, "device allocation failed");
   }
   if (hipMemset(n->d_params, 0, bytes) != hipSuccess || hipMemset(n->d_m, 0, bytes) != hipSuccess ||
-      hipMemset(n->d_v, 0, bytes) != hipSuccess) {
+      hipMemset(n->d_v, 0, bytes) != hipSuccess ||
+      hipMemset(n->d_frags, 0, 2 * (size_t)s.n_frag) != hipSuccess) {
     fib_mlp_destroy(n);
     return mfail(FIB_EHIP, "device initialization failed");
   }
@@ -162,8 +192,8 @@ void fib_mlp_destroy(fib_mlp_t* n) {
   (void)hipFree(n->d_m);
   (void)hipFree(n->d_v);
   (void)hipFree(n->d_grad);
-  (void)hipFree(n->d_part);
-  (void)hipFree(n->d_loss_part);
+  (void)hipFree(n->d_frags);
+  (void)hipFree(n->d_work);
   delete n;
 }
 
@@ -173,6 +203,7 @@ int fib_mlp_set_params(fib_mlp_t* n, const float* params, int64_t count) {
   if (!n || !params) return mfail(FIB_EINVAL, "null argument");
   if (count != n->shape.n_params) return mfail(FIB_EINVAL, "expected %d parameters", n->shape.n_params);
   MHIP(hipMemcpyAsync(n->d_params, params, sizeof(float) * count, hipMemcpyHostToDevice, n->stream));
+  MHIP(fib::launch_mlp_pack(n->shape, n->d_params, n->d_frags, n->stream));
   MHIP(hipStreamSynchronize(n->stream));
   return FIB_OK;
 }
@@ -187,17 +218,16 @@ int fib_mlp_get_params(fib_mlp_t* n, float* params, int64_t count) {
 
 int fib_mlp_forward(fib_mlp_t* n, const float* X, int64_t B, float* O) {
   if (!n || B < 0 || (B > 0 && (!X || !O))) return mfail(FIB_EINVAL, "bad arguments");
-  MHIP(fib::launch_mlp_forward(n->shape, n->d_params, X, B, O, n->stream));
+  MHIP(fib::launch_mlp_forward(n->shape, n->d_params, n->d_frags, X, B, O, n->stream));
   return FIB_OK;
 }
 
 int fib_mlp_gradient(fib_mlp_t* n, const float* X, const float* T, int64_t B, float* grad,
                      float* loss) {
   if (!n || B < 1 || !X || !T) return mfail(FIB_EINVAL, "bad arguments");
-  const int64_t chunks = (B + fib::kChunk - 1) / fib::kChunk;
-  if (int rc = ensure_parts(n, chunks)) return rc;
-  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, X, T, B, n->d_part, n->d_loss_part,
-                            grad ? grad : n->d_grad, loss, n->stream));
+  if (int rc = ensure_work(n, fib::mlp_pass_chunks(n->shape, B))) return rc;
+  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, n->d_frags, X, T, B, n->d_work,
+                            grad ? grad : n->d_grad, loss, nullptr, n->stream));
   return FIB_OK;
 }
 
@@ -206,17 +236,15 @@ int fib_mlp_gradient_noalloc(fib_mlp_t* n, const float* X, const float* T, int64
   if (!n || B < 1 || !X || !T) return mfail(FIB_EINVAL, "bad arguments");
   const int64_t chunks = (B + fib::kChunk - 1) / fib::kChunk;
   const int64_t need = chunks * (int64_t)n->shape.n_params + chunks;
-  if (need > kScratchFloats)
+  if (need > kNoallocFloats)
     return mfail(FIB_EINVAL, "batch of %lld samples needs %lld scratch floats, more than the "
                  "%lld this entry point holds (at most %lld samples for this network)",
-                 (long long)B, (long long)need, (long long)kScratchFloats,
-                 (long long)(kScratchFloats / (n->shape.n_params + 1) * fib::kChunk));
+                 (long long)B, (long long)need, (long long)kNoallocFloats,
+                 (long long)(kNoallocFloats / (n->shape.n_params + 1) * fib::kChunk));
   float* base = scratch_of(n->device);
   if (!base) return mfail(FIB_ESTATE, "scratch of device %d not set up", n->device);
-  float* part = base;
-  float* loss_part = base + chunks * (int64_t)n->shape.n_params;
-  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, X, T, B, part, loss_part,
-                            grad ? grad : n->d_grad, loss, n->stream));
+  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, n->d_frags, X, T, B, base,
+                            grad ? grad : n->d_grad, loss, nullptr, n->stream));
   return FIB_OK;
 }
 
@@ -283,13 +311,12 @@ int fib_normalize_rows(const float* A, int64_t rows, int32_t cols, const float* 
 int fib_mlp_adam_step(fib_mlp_t* n, const float* X, const float* T, int64_t B, double lr,
                       float* loss) {
   if (!n || B < 1 || !X || !T || !(lr > 0.0)) return mfail(FIB_EINVAL, "bad arguments");
-  const int64_t chunks = (B + fib::kChunk - 1) / fib::kChunk;
-  if (int rc = ensure_parts(n, chunks)) return rc;
-  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, X, T, B, n->d_part, n->d_loss_part, n->d_grad,
-                            loss, n->stream));
+  if (int rc = ensure_work(n, fib::mlp_pass_chunks(n->shape, B))) return rc;
+  const fib::MlpAdam adam{n->d_params, n->d_m, n->d_v, n->d_frags, (float)lr, 0.9f, 0.999f, 1e-8f,
+                          n->t + 1};
+  MHIP(fib::launch_mlp_grad(n->shape, n->d_params, n->d_frags, X, T, B, n->d_work, n->d_grad,
+                            loss, &adam, n->stream));
   n->t += 1;
-  MHIP(fib::launch_mlp_adam(n->d_params, n->d_m, n->d_v, n->d_grad, n->shape.n_params, (float)lr,
-                            0.9f, 0.999f, 1e-8f, n->t, n->stream));
   return FIB_OK;
 }
 

@@ -21,17 +21,50 @@ struct MlpShape {
   int w_off[kMaxLayers + 1];    // offset of W_l in the flat parameters
   int b_off[kMaxLayers + 1];    // offset of b_l
   int n_params;
+  // BF16 operand fragments (elements): forward ones of W_l, backward (transposed)
+  // ones of l > 1, and their total
+  int f_off[kMaxLayers + 1];
+  int r_off[kMaxLayers + 1];
+  int n_frag;
+  // operands of the weight gradients a chunk leaves (fragments of 16 features
+  // x 32 samples): the inputs of layer l from a_ops[l], its gradients from
+  // d_ops[l]; the 16 x 16 tiles of all W_l; and all biases, layer l's from
+  // bias_off[l]
+  int a_ops[kMaxLayers + 1];
+  int d_ops[kMaxLayers + 1];
+  int n_ops;
+  int n_tiles;
+  int bias_off[kMaxLayers + 1];
+  int n_bias;
   int act;                      // hidden activation: FIB_ACT_SILU or FIB_ACT_RELU
 };
 
-size_t mlp_train_lds_bytes(const MlpShape& s);
-hipError_t launch_mlp_forward(const MlpShape& s, const float* params, const float* X, int64_t B,
-                              float* O, hipStream_t st);
-hipError_t launch_mlp_grad(const MlpShape& s, const float* params, const float* X, const float* T,
-                           int64_t B, float* part, float* loss_part, float* grad, float* loss,
-                           hipStream_t st);
-hipError_t launch_mlp_adam(float* params, float* m, float* v, const float* grad, int64_t n, float lr,
-                           float b1, float b2, float eps, int64_t t, hipStream_t st);
+// Floats of work space per chunk: its operand fragments (512 BF16 each), bias
+// gradients and loss.
+inline int64_t mlp_chunk_floats(const MlpShape& s) { return (int64_t)s.n_ops * 256 + s.n_bias + 1; }
+// Floats of the allocation-free entry point's fixed scratch: the work space
+// of at least 150 chunks whatever the widths (203 chunks of the 57-128-128-57
+// network's).
+constexpr int64_t kScratchFloats = (int64_t)1 << 23;  // 32 MiB per device
+int mlp_pass_chunks(const MlpShape& s, int64_t B);
+
+// One Adam step: the masters, their moments and fragments.
+struct MlpAdam {
+  float *params, *m, *v;
+  void* frags;
+  float lr, b1, b2, eps;
+  int64_t t;
+};
+
+// BF16 operand fragments of the parameters.
+hipError_t launch_mlp_pack(const MlpShape& s, const float* params, void* frags, hipStream_t st);
+hipError_t launch_mlp_forward(const MlpShape& s, const float* params, const void* frags,
+                              const float* X, int64_t B, float* O, hipStream_t st);
+// Gradient into grad and loss into loss (nullable), and with `adam` the
+// parameter update; work holds mlp_pass_chunks x mlp_chunk_floats values.
+hipError_t launch_mlp_grad(const MlpShape& s, const float* params, const void* frags,
+                           const float* X, const float* T, int64_t B, float* work, float* grad,
+                           float* loss, const MlpAdam* adam, hipStream_t st);
 // Column sums, minima and maxima of A (rows x cols, cols <= 64) into
 // device arrays sum/cmin/cmax; with `mean` (device) also the sums of
 // squared deviations into sq.  part/pmin/pmax hold blocks x cols.
