@@ -386,8 +386,9 @@ int fib_mlp_reset_optimizer(fib_mlp_t* net);
  * rows x cols FP32, row-major, 1 <= cols <= 64) on `stream`: the mean and
  * the sample standard deviation (two passes, FP64 sums in a fixed order, so
  * the result is deterministic) and the minimum and maximum, into host
- * arrays of cols values.  Allocates and frees a small device buffer;
- * blocking. */
+ * arrays of cols values.  Its work space is a fixed array of the library's
+ * code object on the current device: calls on one device take turns.
+ * Blocking. */
 int fib_column_stats(const float* A, int64_t rows, int32_t cols, void* stream, double* mean,
                      double* std, float* cmin, float* cmax);
 

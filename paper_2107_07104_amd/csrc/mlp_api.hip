@@ -38,6 +38,10 @@ struct fib_mlp {
 // below.  Every call on a device shares that device's array.
 static __device__ __align__(256) float scratch[fib::kScratchFloats];
 
+// Work space of fib_column_stats, one per device (its address as above); a
+// call holds its device's lock while it uses it.
+static __device__ __align__(256) char col_work[sizeof(fib::ColWork)];
+
 // Batches fib_mlp_gradient_noalloc takes: ceil(B / 32) (n_params + 1) floats
 // at most.
 static constexpr int64_t kNoallocFloats = (int64_t)1 << 22;
@@ -68,6 +72,7 @@ int mfail(int code, const char* fmt, ...) {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 float* g_scratch[kMaxDevices] = {};
+std::mutex g_col_mu[kMaxDevices];
 
 // Looks up (once) the scratch address of `dev`, which must be current.
 int scratch_setup(int dev) {
@@ -250,60 +255,43 @@ int fib_mlp_gradient_noalloc(fib_mlp_t* n, const float* X, const float* T, int64
 
 int fib_column_stats(const float* A, int64_t rows, int32_t cols, void* stream, double* mean,
                      double* std, float* cmin, float* cmax) {
-  if (!A || rows < 1 || cols < 1 || cols > 64 || !mean || !std || !cmin || !cmax)
+  if (!A || rows < 1 || cols < 1 || cols > fib::kStatCols || !mean || !std || !cmin || !cmax)
     return mfail(FIB_EINVAL, "bad arguments (1 <= cols <= 64, rows >= 1)");
   hipStream_t st = (hipStream_t)stream;
-  const int blocks = (int)std::min<int64_t>(1024, (rows + 255) / 256);
-  double* d = nullptr;
-  float* f = nullptr;
-  const size_t nd = (size_t)blocks * cols + 3 * (size_t)cols, nf = 2 * ((size_t)blocks + 1) * cols;
-  if (hipMalloc(&d, sizeof(double) * nd) != hipSuccess || hipMalloc(&f, sizeof(float) * nf) != hipSuccess) {
-    (void)hipFree(d);
-    return mfail(FIB_ENOMEM, "device allocation failed");
-  }
-  double *part = d, *sum = part + (size_t)blocks * cols, *mu = sum + cols, *sq = mu + cols;
-  float *pmin = f, *pmax = pmin + (size_t)blocks * cols, *lo = pmax + (size_t)blocks * cols,
-        *hi = lo + cols;
-  std::vector<double> hsum(cols), hsq(cols);
-  int rc = FIB_OK;
-  hipError_t e = fib::launch_col_stats(A, rows, cols, part, pmin, pmax, blocks, sum, lo, hi,
-                                       nullptr, nullptr, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(hsum.data(), sum, sizeof(double) * cols, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess) {
-    for (int k = 0; k < cols; ++k) mean[k] = hsum[k] / (double)rows;
-    e = hipMemcpyAsync(mu, mean, sizeof(double) * cols, hipMemcpyHostToDevice, st);
-  }
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
+    return mfail(FIB_EHIP, "no HIP device");
+  // the call waits for its results, so it holds its device's work space
+  // until then
+  std::lock_guard<std::mutex> lock(g_col_mu[dev]);
+  void* w = nullptr;
+  hipError_t e = hipGetSymbolAddress(&w, HIP_SYMBOL(col_work));
   if (e == hipSuccess)
-    e = fib::launch_col_stats(A, rows, cols, part, pmin, pmax, blocks, sum, lo, hi, mu, sq, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(hsq.data(), sq, sizeof(double) * cols, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(cmin, lo, sizeof(float) * cols, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(cmax, hi, sizeof(float) * cols, hipMemcpyDeviceToHost, st);
+    e = fib::launch_col_stats(A, rows, cols, static_cast<fib::ColWork*>(w), st);
+  fib::ColStats h;
+  if (e == hipSuccess) e = hipMemcpyAsync(&h, w, sizeof h, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess) {
-    for (int k = 0; k < cols; ++k) std[k] = rows > 1 ? std::sqrt(hsq[k] / (double)(rows - 1)) : 0.0;
-  } else {
-    rc = mfail(FIB_EHIP, "column statistics: %s", hipGetErrorString(e));
+  if (e != hipSuccess) return mfail(FIB_EHIP, "column statistics: %s", hipGetErrorString(e));
+  for (int k = 0; k < cols; ++k) {
+    mean[k] = h.mean[k];
+    std[k] = rows > 1 ? std::sqrt(h.sq[k] / (double)(rows - 1)) : 0.0;
+    cmin[k] = h.lo[k];
+    cmax[k] = h.hi[k];
   }
-  (void)hipFree(d);
-  (void)hipFree(f);
-  return rc;
+  return FIB_OK;
 }
 
 int fib_normalize_rows(const float* A, int64_t rows, int32_t cols, const float* shift,
                        const float* scale, double extra, float* Y, int32_t ldy, void* stream) {
-  if (!A || !Y || !shift || !scale || rows < 0 || cols < 1 || cols > 64 || ldy < cols)
+  if (!A || !Y || !shift || !scale || rows < 0 || cols < 1 || cols > fib::kStatCols || ldy < cols)
     return mfail(FIB_EINVAL, "bad arguments (1 <= cols <= 64, ldy >= cols)");
   if (rows == 0) return FIB_OK;
   hipStream_t st = (hipStream_t)stream;
-  float* d = nullptr;
-  if (hipMalloc(&d, sizeof(float) * 2 * cols) != hipSuccess)
-    return mfail(FIB_ENOMEM, "device allocation failed");
-  hipError_t e = hipMemcpyAsync(d, shift, sizeof(float) * cols, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(d + cols, scale, sizeof(float) * cols, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = fib::launch_normalize(A, rows, cols, d, d + cols, (float)extra, Y, ldy, st);
+  fib::ColScale cs{};
+  std::copy(shift, shift + cols, cs.shift);
+  std::copy(scale, scale + cols, cs.scale);
+  hipError_t e = fib::launch_normalize(A, rows, cols, cs, (float)extra, Y, ldy, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(d);
   if (e != hipSuccess) return mfail(FIB_EHIP, "normalize: %s", hipGetErrorString(e));
   return FIB_OK;
 }

@@ -65,15 +65,27 @@ hipError_t launch_mlp_forward(const MlpShape& s, const float* params, const void
 hipError_t launch_mlp_grad(const MlpShape& s, const float* params, const void* frags,
                            const float* X, const float* T, int64_t B, float* work, float* grad,
                            float* loss, const MlpAdam* adam, hipStream_t st);
-// Column sums, minima and maxima of A (rows x cols, cols <= 64) into
-// device arrays sum/cmin/cmax; with `mean` (device) also the sums of
-// squared deviations into sq.  part/pmin/pmax hold blocks x cols.
-hipError_t launch_col_stats(const float* A, int64_t rows, int cols, double* part, float* pmin,
-                            float* pmax, int blocks, double* sum, float* cmin, float* cmax,
-                            const double* mean, double* sq, hipStream_t st);
+// Column statistics: results, and their work space in device memory.
+constexpr int kStatCols = 64, kStatBlocks = 2048;
+struct ColStats {
+  double mean[kStatCols], sq[kStatCols];  // sq: sum of squared deviations
+  float lo[kStatCols], hi[kStatCols];
+};
+struct ColWork {
+  ColStats stats;
+  double part[kStatBlocks * kStatCols];
+  float pmin[kStatBlocks * kStatCols], pmax[kStatBlocks * kStatCols];
+};
+// Statistics of the columns of A (rows x cols, cols <= kStatCols) into
+// w->stats (two passes over A).
+hipError_t launch_col_stats(const float* A, int64_t rows, int cols, ColWork* w, hipStream_t st);
+// Shift and scale of every column, passed to the kernel by value.
+struct ColScale {
+  float shift[kStatCols], scale[kStatCols];
+};
 // Y[r][k] = (A[r][k] - shift[k]) scale[k]; Y[r][cols] = extra if ldy > cols.
-hipError_t launch_normalize(const float* A, int64_t rows, int cols, const float* shift,
-                            const float* scale, float extra, float* Y, int ldy, hipStream_t st);
+hipError_t launch_normalize(const float* A, int64_t rows, int cols, const ColScale& cs, float extra,
+                            float* Y, int ldy, hipStream_t st);
 
 }  // namespace fib
 
