@@ -283,6 +283,8 @@ struct fib_ctx {
   std::vector<int32_t> node_stim;      // host copy: stimulus entry + 1 per node (0: none)
   bool state_ready = false;
   bool tune_pending = false;  // fib_params.tune: autotune before the first run
+  bool tuned = false;         // the plan's shape is the autotuner's
+  bool adapt_planned = false; // the plan was chosen for the adaptive fused kernel
 
   // surrogate
   bool sur_on = false;
@@ -788,6 +790,85 @@ int adapt_fused_tables(fib_ctx* c, bool* ok) {
   c->adapt_fused_ok = true;
   *ok = true;
   return FIB_OK;
+}
+
+// Workgroup shape of the fused kernels for bins of `load` nodes, among those
+// `fits` takes: the fewest slots one SIMD sweeps per step, ceil(T / 256) K,
+// which orders the measured times (the 1369-fiber bundle's bins of 6701
+// nodes, us per 200 steps: 768 x 9 27 slots 2439, 960 x 7 28 2513, 1024 x 7 28
+// 2520, 512 x 14 28 2630, 704 x 10 30 2703, 896 x 8 32 2879); of equals the
+// larger workgroup (one fiber of 1000 nodes: 512 x 2 257 us, 256 x 4 283 per
+// 100 steps).  T = K = 0 if no shape holds the load.
+template <class Fits>
+void fused_shape(int64_t load, Fits fits, int& T, int& K) {
+  T = K = 0;
+  int64_t best = INT64_MAX;
+  for (int k = 2; k <= 14; ++k) {
+    const int64_t t = std::max<int64_t>(64, (load + 64LL * k - 1) / (64LL * k) * 64);
+    if (t > fib::plan_max_threads(k) || !fits((int)t, k)) continue;
+    const int64_t cost = (t + 255) / 256 * k;
+    if (cost < best || (cost == best && t > T)) {
+      best = cost;
+      T = (int)t;
+      K = k;
+    }
+  }
+}
+
+// Adaptive computation on automatic shapes, schedule AUTO: the plain plan may
+// not fit the adaptive fused kernel, whose states live in LDS (1024 x 7 slots
+// need 170 KB), and the split schedule it would fall back to takes three
+// launches per step (1369 fibers, 200 steps: 7.3 ms against 2.4 ms fused).  So
+// the shape, and if no shape of these bins fits, more and smaller bins, are
+// chosen for that kernel; fib_set_adaptive(0) returns to the plain plan.
+// Where nothing fits the plan stays.  The stream must be idle.
+int adapt_plan(fib_ctx* c, bool on) {
+  const bool automatic = c->p.schedule == FIB_SCHED_AUTO && c->p.model == FIB_MODEL_HH &&
+                         c->p.threads_per_group == 0 && c->p.nodes_per_thread == 0 &&
+                         c->p.groups == 0 && !c->tuned && c->n_total > 0;
+  if (!automatic || on == c->adapt_planned) return FIB_OK;
+  const size_t old = std::max<size_t>(c->slot_gidx.size(), 1);
+  if (!on) {
+    c->adapt_planned = false;
+    if (int rc = make_plan(c)) return rc;
+    return upload_plan(c, old);
+  }
+  auto holds = [&]() {
+    for (auto& b : c->bin_fibers)
+      if ((int)b.size() > fib::kBinFibers) return false;
+    return fib::lds_bytes_for(c->threads, c->levels) + fib::adapt_lds_extra(c->cap) <= c->max_lds;
+  };
+  if (holds()) return FIB_OK;
+  for (int groups = c->groups;; groups = std::min(2 * groups, c->n_fibers)) {
+    if (groups != c->groups) {
+      pack_bins(c, groups);
+      c->groups = groups;
+    }
+    const int64_t load = max_bin_load(c);
+    std::vector<std::pair<int, int>> no;  // shapes whose PCR levels take too much LDS
+    for (bool found = true; found && !c->adapt_planned;) {
+      int T, K;
+      fused_shape(load,
+                  [&](int t, int k) {
+                    return fib::lds_bytes_for(t, 0) + fib::adapt_lds_extra(t * k) <= c->max_lds &&
+                           std::find(no.begin(), no.end(), std::make_pair(t, k)) == no.end();
+                  },
+                  T, K);
+      found = K > 0;
+      if (!found) break;
+      c->threads = T;
+      c->K = K;
+      build_tables(c);
+      c->adapt_planned = holds();
+      no.push_back({T, K});
+    }
+    if (c->adapt_planned) break;
+    if (groups >= c->n_fibers) {  // nothing fits: the plain plan again
+      if (int rc = make_plan(c)) return rc;
+      return upload_plan(c, old);
+    }
+  }
+  return upload_plan(c, old);
 }
 
 // The point flags of step step0 - 1 must sit in buffer (step0 - 1) & 1.
@@ -1740,6 +1821,7 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
   }
   if (copy_all(false) != hipSuccess && !rc) rc = fail(FIB_EHIP, "autotune: state copy failed");
   cleanup();
+  if (!rc) c->tuned = true;
   if (!rc && ms_per_step) *ms_per_step = best / trial_steps;
   return rc;
 }
@@ -1965,7 +2047,9 @@ int fib_set_adaptive(fib_t* c, double tol) {
   if (!(std::isfinite(tol) && tol >= 0.0)) return fail(FIB_EINVAL, "tol must be finite and >= 0");
   if (tol == 0.0) {
     c->adapt_tol = 0.0;
-    return FIB_OK;
+    if (!c->adapt_planned) return FIB_OK;
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return adapt_plan(c, false);
   }
   if (c->sur_on)
     return fail(FIB_EUNSUPPORTED, "adaptive computation and the surrogate step do not combine");
@@ -2004,6 +2088,7 @@ int fib_set_adaptive(fib_t* c, double tol) {
       return fail(FIB_ENOMEM, "device allocation failed");
     }
   }
+  if (int rc = adapt_plan(c, true)) return rc;
   if (c->n_fibers > 0)
     HIP_TRY(hipMemcpy(c->d_first_on, c->first_on.data(), sizeof(int32_t) * c->n_fibers,
                       hipMemcpyHostToDevice));
