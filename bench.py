@@ -139,9 +139,10 @@ ST57_REACT_OPS = 6 * ST57_HEUN_OPS
 ST57_OPS_PER_NODE_STEP = ST57_REACT_OPS + 13
 
 # EMG conjugate-gradient iteration, per mesh node (FP32 vectors): the
-# stencil launch reads r, 1/diag, p_old and writes p, q (20 B); the update
-# launch reads p, q, 1/diag, x, r and writes x, r (28 B)
-EMG_BYTES_PER_NODE_ITERATION = 48
+# transforms read r and write u (8 B), read and write u (8 B), read u and r
+# and write z (12 B); the stencil launch reads z, p_old and writes p, q (16 B);
+# the update launch reads p, q, x, r and writes x, r (24 B)
+EMG_BYTES_PER_NODE_ITERATION = 68
 
 HBM_PEAK = 8.0e12
 MFMA_BF16_PEAK = 2.5e15
@@ -1064,7 +1065,7 @@ def emg_bench(args):
     # so right-hand side, start, host checks and the final shift count too
     gbs = EMG_BYTES_PER_NODE_ITERATION * g.n * tot_it / t_emg / 1e9
     roof = dict(bound="hbm", achieved=gbs, peak=HBM_PEAK / 1e9, unit="GB/s",
-                frac=gbs * 1e9 / HBM_PEAK, traffic=None, kernel="k_cg_q + k_cg_x",
+                frac=gbs * 1e9 / HBM_PEAK, traffic=None, kernel="k_fdm_xy + k_fdm_z + k_fdm_back + k_pcg_q + k_pcg_x",
                 bytes_per_node_iteration=EMG_BYTES_PER_NODE_ITERATION,
                 timing="whole EMG solves (host clock around synchronized solves)")
     out = dict(workload=f"hh_emg_{nf}x{nf}x{n}, 3D mesh {nf}x{nf}x{g.nz}, solve every {every} "

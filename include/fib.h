@@ -564,8 +564,10 @@ int fib_emg_dims(const fib_emg_t* emg, int32_t* nx, int32_t* ny, int32_t* nz);
 /* One static bidomain solve from the context's current V_m, on its stream:
  * right-hand side b = -K_{sigma_i} P V_m (V_m taken relative to the
  * resting potential, which K_{sigma_i} annihilates), projected to zero mean;
- * then conjugate gradients with the diagonal of K_{sigma_i + sigma_e} as
- * preconditioner, started from the last phi_e, with the residual kept at
+ * then preconditioned conjugate gradients (the preconditioner is the inverse
+ * of K_{sigma_i + sigma_e} by FP32 cosine transforms where nx, ny <= 128 and
+ * there are at most 2048 layers, else its diagonal), started from the last
+ * phi_e, with the residual kept at
  * zero mean (the range of the singular Neumann operator) in every
  * iteration, until ||r||_2 <= tol ||b||_2 or max_iter iterations; phi_e is
  * returned to zero mean.  FP32 vectors, FP64 reductions; tolerances down to
