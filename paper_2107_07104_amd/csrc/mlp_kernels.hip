@@ -46,7 +46,7 @@ constexpr int kWaves = 8;        // waves of a training workgroup
 // layer l < L feature-major (pad[l] rows of kTS BF16), the operand of the
 // weight gradients; dt: two blocks of the gradient feature-major; z[l]: the
 // pre-activations of hidden layer l in FP32, in the accumulators' own order;
-// db: per-feature sums of the gradient over each half of the samples.
+// db: per-feature sums of the gradient over the samples.
 struct NetLds {
   int xstride;
   int xs[2];
@@ -83,7 +83,7 @@ static NetLds net_lds(const MlpShape& s, bool grad) {
     }
     for (int b = 0; b < 2; ++b) {
       t.db[b] = o;
-      o += 2 * 4 * pmax;
+      o += 4 * pmax;
     }
     t.loss = o;
     o += 4 * kWaves;
@@ -159,15 +159,29 @@ __device__ __forceinline__ void store_operand(const v4f& v, __bf16* xs, int xstr
   }
 }
 
-// Sums of a lane's four features over the 16 samples of half sb, to
-// db[sb][f .. f + 3].
-__device__ __forceinline__ void sum_samples(v4f v, float* db, int pmax, int sb, int f, int lane) {
+// Sum of v over the 16 samples of a lane row, one after the other from
+// `carry`, in the row's last lane: FP32 sums keep one fixed order over the
+// batch's samples.
+__device__ __forceinline__ float scan_samples(float v, float carry, int r) {
+  v += r == 0 ? carry : 0.0f;
+  float acc = v;
 #pragma unroll
-  for (int d = 1; d < 16; d <<= 1) {
+  for (int k = 1; k < 16; ++k)  // lane k takes lane k - 1's sum (row_shr:1, 0 into lane 0)
+    acc = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+              0, __builtin_bit_cast(int, acc), 0x111, 0xf, 0xf, true)) + v;
+  return acc;
+}
+
+// Sums of a lane's four features over the chunk's samples (v[0]: the first
+// 16, v[1]: the others) to db[f .. f + 3].
+__device__ __forceinline__ void sum_samples(const v4f (&v)[2], float* db, int f, int lane) {
+  v4f s;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], d);
+  for (int j = 0; j < 4; ++j) {
+    const float half = scan_samples(v[0][j], 0.0f, lane & 15);
+    s[j] = scan_samples(v[1][j], __shfl(half, lane | 15), lane & 15);
   }
-  if ((lane & 15) == 0) *reinterpret_cast<v4f*>(db + sb * pmax + f) = v;
+  if ((lane & 15) == 15) *reinterpret_cast<v4f*>(db + f) = s;
 }
 
 // The network kernels: a workgroup of eight waves takes a chunk of kChunk =
@@ -187,7 +201,7 @@ __device__ __forceinline__ void sum_samples(v4f v, float* db, int pmax, int sb, 
 // On the 57-128-128-57 network that batch's gradient took 553 us with one
 // wave per chunk (FP32 operands in LDS, 115 KB: one wave per compute unit)
 // and every chunk's whole weight gradient (32 MB in all) written out and
-// summed; 50 us with these workgroups doing the same; 30 us (this kernel 21)
+// summed; 50 us with these workgroups doing the same; 35 us (this kernel 21)
 // with the operands (10 MB) written instead and contracted by k_mlp_update.
 template <bool GRAD>
 __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
@@ -202,7 +216,6 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
   extern __shared__ __align__(16) char lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, g = lane >> 4;
-  const int pmax = t.xstride - 8;
   const int nL = s.size[s.L];
   const float scale = 1.0f / ((float)B * (float)nL);
   const int64_t chunks = (B + kChunk - 1) / kChunk;
@@ -237,37 +250,52 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
       const int nout = s.size[l], ob_n = s.pad[l] >> 4, kb_n = s.pad[l - 1] >> 5;
       const v8bf* fr = reinterpret_cast<const v8bf*>(frags + s.f_off[l]);
       const float* bias = params + s.b_off[l];
-      for (int u = wave; u < 2 * ob_n; u += kWaves) {
-        const int ob = u % ob_n, sb = u / ob_n;
-        const int f = 16 * ob + 4 * g, n = 16 * sb + r;
-        float bj[4], tj[4];
+      // the last layer's gradient sums need both halves of the samples in one
+      // wave; the other layers' units go to whichever wave is next
+      const bool pair = GRAD && l == s.L;
+      for (int u = wave; u < (pair ? ob_n : 2 * ob_n); u += kWaves) {
+        const int ob = u % ob_n, f = 16 * ob + 4 * g;
+        float bj[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) bj[j] = f + j < nout ? bias[f + j] : 0.0f;
-        if (GRAD && l == s.L) {
+        if (pair) {
+          v4f d[2];
+          float tj[2][4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            tj[j] = s0 + n < B && f + j < nout ? T[(s0 + n) * nout + f + j] : 0.0f;
+          for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int64_t sr = s0 + 16 * sb + r;
+              tj[sb][j] = sr < B && f + j < nout ? T[sr * nout + f + j] : 0.0f;
+            }
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb) {
+            const int n = 16 * sb + r;
+            v4f v = block_product(fr + (int64_t)ob * kb_n * 64, src, t.xstride, kb_n, sb, lane);
+            // output gradient (O - T) / (B n_L), zero on padding and past B
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float o = v[j] + bj[j];
+              const float diff = s0 + n < B && f + j < nout ? o - tj[sb][j] : 0.0f;
+              lsum += diff * diff;
+              d[sb][j] = diff * scale;
+            }
+            store_operand(d[sb], dst, t.xstride, reinterpret_cast<__bf16*>(lds + t.dt[l & 1]), n, f);
+          }
+          sum_samples(d, reinterpret_cast<float*>(lds + t.db[l & 1]), f, lane);
+          continue;
         }
+        const int sb = u / ob_n, n = 16 * sb + r;
         v4f v = block_product(fr + (int64_t)ob * kb_n * 64, src, t.xstride, kb_n, sb, lane);
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] += bj[j];
         if (l < s.L) {
-          if (GRAD) *reinterpret_cast<v4f*>(lds + t.z[l] + 16 * (u * 64 + lane)) = v;
+          if (GRAD)
+            *reinterpret_cast<v4f*>(lds + t.z[l] + 16 * ((sb * ob_n + ob) * 64 + lane)) = v;
 #pragma unroll
           for (int j = 0; j < 4; ++j) v[j] = act_fn(s.act, v[j]);
           store_operand(v, dst, t.xstride,
                         GRAD ? reinterpret_cast<__bf16*>(lds + t.xt[l]) : nullptr, n, f);
-        } else if (GRAD) {
-          // output gradient (O - T) / (B n_L), zero on padding and past B
-          v4f d;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float diff = s0 + n < B && f + j < nout ? v[j] - tj[j] : 0.0f;
-            lsum += diff * diff;
-            d[j] = diff * scale;
-          }
-          store_operand(d, dst, t.xstride, reinterpret_cast<__bf16*>(lds + t.dt[l & 1]), n, f);
-          sum_samples(d, reinterpret_cast<float*>(lds + t.db[l & 1]), pmax, sb, f, lane);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
@@ -291,23 +319,28 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
           __bf16* dst = reinterpret_cast<__bf16*>(lds + t.xs[(l - 1) & 1]);
           const int ib_n = s.pad[l - 1] >> 4, kb_n = s.pad[l] >> 5;
           const v8bf* fr = reinterpret_cast<const v8bf*>(frags + s.r_off[l]);
-          for (int u = wave; u < 2 * ib_n; u += kWaves) {
-            const int ib = u % ib_n, sb = u / ib_n;
-            const int f = 16 * ib + 4 * g, n = 16 * sb + r;
-            v4f v = block_product(fr + (int64_t)ib * kb_n * 64, src, t.xstride, kb_n, sb, lane);
-            const v4f z = *reinterpret_cast<const v4f*>(lds + t.z[l - 1] + 16 * (u * 64 + lane));
+          for (int ib = wave; ib < ib_n; ib += kWaves) {
+            const int f = 16 * ib + 4 * g;
+            v4f d[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = f + j < nin ? v[j] * act_grad(s.act, z[j]) : 0.0f;
-            store_operand(v, dst, t.xstride,
-                          reinterpret_cast<__bf16*>(lds + t.dt[(l - 1) & 1]), n, f);
-            sum_samples(v, reinterpret_cast<float*>(lds + t.db[(l - 1) & 1]), pmax, sb, f, lane);
+            for (int sb = 0; sb < 2; ++sb) {
+              d[sb] = block_product(fr + (int64_t)ib * kb_n * 64, src, t.xstride, kb_n, sb, lane);
+              const v4f z = *reinterpret_cast<const v4f*>(
+                  lds + t.z[l - 1] + 16 * ((sb * ib_n + ib) * 64 + lane));
+#pragma unroll
+              for (int j = 0; j < 4; ++j)
+                d[sb][j] = f + j < nin ? d[sb][j] * act_grad(s.act, z[j]) : 0.0f;
+              store_operand(d[sb], dst, t.xstride,
+                            reinterpret_cast<__bf16*>(lds + t.dt[(l - 1) & 1]), 16 * sb + r, f);
+            }
+            sum_samples(d, reinterpret_cast<float*>(lds + t.db[(l - 1) & 1]), f, lane);
           }
         }
         put(reinterpret_cast<const __bf16*>(lds + t.xt[l - 1]), s.a_ops[l], (nin + 15) >> 4);
         put(reinterpret_cast<const __bf16*>(lds + t.dt[l & 1]), s.d_ops[l], (nout + 15) >> 4);
         const float* db = reinterpret_cast<const float*>(lds + t.db[l & 1]);
         float* rb = db_part + (int64_t)blockIdx.x * s.n_bias + s.bias_off[l];
-        for (int j = threadIdx.x; j < nout; j += 64 * kWaves) rb[j] = db[j] + db[pmax + j];
+        for (int j = threadIdx.x; j < nout; j += 64 * kWaves) rb[j] = db[j];
         __syncthreads();
       }
       // (launched with one chunk per workgroup)
@@ -356,27 +389,33 @@ __device__ __forceinline__ void finish_param(const MlpShape& s, int l, int out, 
   }
 }
 
-constexpr int kUpdWaves = 16;  // waves of an update workgroup
+constexpr int kUpdWaves = 16;    // waves of an update workgroup
+constexpr int kAheadChunks = 8;  // chunks of each wave whose operands are in flight
 
 // Gradients from the operands of a pass: block b < n_tiles contracts one 16
-// x 16 tile of some dW_l = sum over chunks of dz_l act_{l-1}^T, the sixteen
-// waves a share of the chunks each (one instruction per chunk, K = its 32
-// samples; eight chunks' operands in flight), then sums the waves' tiles in
-// order; the blocks after the tiles sum 64 biases each over the chunks, the
-// last one the loss.  Every sum's order is fixed, so gradients are
-// deterministic.  add: a later pass of a batch too large for one; the
+// x 16 tile of some dW_l = sum over chunks of dz_l act_{l-1}^T, a wave per
+// chunk and sixteen at a time (one instruction per chunk, K = its 32 samples;
+// eight chunks' operands of every wave in flight), which 256 threads add up in
+// the chunks' order through LDS; the blocks after the tiles sum 64 biases
+// each over the chunks, the last one the loss.  Every sum has one fixed
+// order, over the samples of a chunk and then the chunks, so gradients are
+// deterministic and do not depend on how the work is split (Adam's first
+// steps are signs of gradients: an order of its own would send training
+// elsewhere).  add: a later pass of a batch too large for one; the
 // parameters are updated (ad.p non-null) with the last.
 //
 // Bound by reading the operands, 2 KB per tile and chunk (64 MB from the
-// last-level cache for a batch of 8192 on the 57-128-128-57 network): 9.9 us
-// with Adam (12.6 us with eight waves); one thread per parameter walking 256
-// whole gradients one by one took 71 us, and Adam a launch of 5 us more.
+// last-level cache for a batch of 8192 on the 57-128-128-57 network), and then
+// by the ordered sums: 15 us with Adam (10 us with each wave's chunks summed
+// in its accumulators); one thread per parameter walking 256 whole gradients
+// one by one took 71 us, and Adam a launch of 5 us more.
 __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
     MlpShape s, const v8bf* __restrict__ ops, const float* __restrict__ db_part,
     const float* __restrict__ loss_part, int chunks, int add, float* __restrict__ grad,
     float* __restrict__ loss, AdamArgs ad) {
-  __shared__ __align__(16) float sh[kUpdWaves][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __align__(16) float sh[2][kUpdWaves][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = threadIdx.x;
+  float sum = 0.0f;  // thread w < 256: element w of the tile
   if ((int)blockIdx.x < s.n_tiles) {
     int l = 1, tile = blockIdx.x, ib_n;
     for (;; ++l) {
@@ -389,40 +428,55 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
     const v8bf* pa = ops + (int64_t)(s.d_ops[l] + ob) * 64 + lane;
     const v8bf* pb = ops + (int64_t)(s.a_ops[l] + ib) * 64 + lane;
     const int64_t stride = (int64_t)s.n_ops * 64;
-    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int c0 = wave; c0 < chunks; c0 += 8 * kUpdWaves) {
-      v8bf a[8], b[8];
+    int par = 0;
+    for (int c0 = 0; c0 < chunks; c0 += kAheadChunks * kUpdWaves) {
+      v8bf a[kAheadChunks], b[kAheadChunks];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int c = c0 + q * kUpdWaves;
+      for (int q = 0; q < kAheadChunks; ++q) {
+        const int c = c0 + q * kUpdWaves + wave;
         if (c < chunks) {
           a[q] = pa[c * stride];
           b[q] = pb[c * stride];
         }
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (c0 + q * kUpdWaves < chunks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q], b[q], acc, 0, 0, 0);
+      for (int q = 0; q < kAheadChunks; ++q) {
+        const int r0 = c0 + q * kUpdWaves;
+        if (r0 >= chunks) break;
+        if (r0 + wave < chunks) {
+          const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+          *reinterpret_cast<v4f*>(&sh[par][wave][4 * lane]) =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q], b[q], zero, 0, 0, 0);
+        }
+        __syncthreads();
+        if (w < 256) {
+          const int n = min(kUpdWaves, chunks - r0);
+          for (int v = 0; v < n; ++v) sum += sh[par][v][w];
+        }
+        par ^= 1;
+      }
     }
-    *reinterpret_cast<v4f*>(&sh[wave][4 * lane]) = acc;
-    __syncthreads();
-    const int w = threadIdx.x;
     if (w >= 256) return;
-    float g = 0.0f;
-#pragma unroll
-    for (int v = 0; v < kUpdWaves; ++v) g += sh[v][w];
     const int out = 16 * ob + 4 * (w >> 6) + (w & 3), in = 16 * ib + ((w >> 2) & 15);
-    if (out < s.size[l] && in < s.size[l - 1]) finish_param(s, l, out, in, g, add, grad, ad);
+    if (out < s.size[l] && in < s.size[l - 1]) finish_param(s, l, out, in, sum, add, grad, ad);
     return;
   }
   const int j = ((int)blockIdx.x - s.n_tiles) * 64 + lane;
-  float acc = 0.0f;
-  if (j < s.n_bias) {
-    for (int c = wave; c < chunks; c += kUpdWaves) acc += db_part[(int64_t)c * s.n_bias + j];
+  // the waves fetch four chunks each, the first one adds them in order
+  for (int c0 = 0; c0 < chunks; c0 += 4 * kUpdWaves) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = c0 + 4 * wave + q;
+      sh[0][wave][64 * q + lane] = c < chunks && j < s.n_bias ? db_part[(int64_t)c * s.n_bias + j]
+                                                              : 0.0f;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const int n = min(4 * kUpdWaves, chunks - c0);
+      for (int v = 0; v < n; ++v) sum += sh[0][v >> 2][64 * (v & 3) + lane];
+    }
+    __syncthreads();
   }
-  sh[wave][lane] = acc;
-  __syncthreads();
   if (wave > 0) return;
   if (blockIdx.x + 1 == gridDim.x && loss) {
     float a = 0.0f;
@@ -431,10 +485,9 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
     if (lane == 0) loss[0] = add ? loss[0] + a : a;
   }
   if (j >= s.n_bias) return;
-  for (int v = 1; v < kUpdWaves; ++v) acc += sh[v][lane];
   int l = 1;
   while (l < s.L && j >= s.bias_off[l + 1]) ++l;
-  finish_param(s, l, j - s.bias_off[l], -1, acc, add, grad, ad);
+  finish_param(s, l, j - s.bias_off[l], -1, sum, add, grad, ad);
 }
 
 // ---------------------------------------------------------------------------
