@@ -80,9 +80,11 @@ enum { FIB_MODEL_HH = 0, FIB_MODEL_ST57 = 1, FIB_MODEL_HH_APX_EXP = 2, FIB_MODEL
 /* Execution schedule of fib_run.
  *   FUSED: one persistent kernel keeps every node's states in registers and
  *          every fiber's V_m exchange in LDS for all split steps of the call.
- *   SPLIT: one reaction kernel and one diffusion kernel per split step with
- *          states in device memory.
- *   AUTO:  FUSED where the model fits it (Hodgkin-Huxley), else SPLIT. */
+ *   SPLIT: states in device memory: one reaction kernel and one diffusion
+ *          kernel per split step, or, for Hodgkin-Huxley, kernels that each
+ *          take a few whole split steps on overlapping windows of nodes;
+ *   AUTO:  for Hodgkin-Huxley FUSED, or the windows where those are faster
+ *          (few or short fibers, no workgroup shape given), else SPLIT. */
 enum { FIB_SCHED_AUTO = 0, FIB_SCHED_FUSED = 1, FIB_SCHED_SPLIT = 2 };
 
 /* Operator splitting of a split step of width dt = dt_split.
@@ -491,8 +493,10 @@ int fib_graph_replays(fib_t* ctx, int64_t* n);
 /* Kernel timing for measurement.  With timing on, fib_run and
  * fib_step_surrogate record a HIP event on the context's stream before and
  * after each kernel launch of these classes:
- *   FUSED:      the persistent split-step kernel (one launch per fib_run);
- *   REACTION:   reaction launches of the split schedule;
+ *   FUSED:      the persistent split-step kernel (one launch per fib_run), or
+ *               the window launches that take its place under AUTO;
+ *   REACTION:   reaction launches of the split schedule, or its window
+ *               launches;
  *   DIFFUSION:  diffusion launches of the split schedule;
  *   SURROGATE:  the surrogate step kernel (network or closed-form predictor);
  *   FALLBACK:   the plain Heun pair on the rejected nodes.

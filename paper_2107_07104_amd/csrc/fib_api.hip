@@ -286,6 +286,17 @@ struct fib_ctx {
   bool tuned = false;         // the plan's shape is the autotuner's
   bool adapt_planned = false; // the plan was chosen for the adaptive fused kernel
 
+  // windowed diffusion: its stencil for the split step's substep where it
+  // applies (width > 0), the distances to the fibers' ends, the row the
+  // reaction kernels leave V_m in for it, and for whole steps on windows
+  // (Hodgkin-Huxley) the second buffer of states and the plan
+  fib::WindowStencil win{};
+  uint16_t* d_ends = nullptr;
+  float* d_vmid = nullptr;
+  float* d_alt = nullptr;
+  fib::WindowPlan win_plan{};
+  bool win_auto = false;      // schedule AUTO takes windows, not the fused kernel
+
   // surrogate
   bool sur_on = false;
   fib::SurrogateNet sur_net{};
@@ -720,6 +731,8 @@ KArgs base_args(const fib_ctx* c) {
   a.stim = c->d_stim;
   a.t_act = c->d_tact;
   a.v_prev = c->d_vprev;
+  a.node_ends = c->d_ends;
+  a.v_out = c->d_state;
   a.flag = c->d_flag;
   a.cap = c->cap;
   a.inv_cm = (float)(1.0 / c->p.Cm);
@@ -727,6 +740,95 @@ KArgs base_args(const fib_ctx* c) {
   a.dt = (float)c->p.dt_split;
   for (int k = 0; k < c->S; ++k) a.rest[k] = (float)c->rest[k];
   return a;
+}
+
+// The windowed diffusion of a context: one substep per split step, a stencil
+// within the built widths, and no fiber shorter than its reflections reach
+// (pcr_full asks for the partitioned solve in full).
+void window_rule(fib_ctx* c) {
+  c->win = fib::WindowStencil{};
+  if (c->p.pcr_full || c->n_fibers == 0 || ceil_steps(c->p.dt_split, c->p.dt_1D) != 1) return;
+  const double theta = theta_of(c->p);
+  fib::WindowStencil st;
+  if (!fib::window_stencil(theta * cn_r(c, c->p.dt_split), theta, st)) return;
+  if (*std::min_element(c->n_nodes.begin(), c->n_nodes.end()) <= st.width) return;
+  c->win = st;
+}
+
+// Threads per block and steps per launch of whole Hodgkin-Huxley steps on
+// windows, and their estimated cycles per split step.  A launch of S steps
+// computes halo = S width nodes beyond a block's own at either side, so more
+// steps share a launch's fixed cost but more nodes are computed twice.  The
+// costs are measured: about 1100 cycles per step for each wave a SIMD holds
+// (at least 1500, one wave's own chain), 300 for the exchange, and 9000 per
+// launch.
+double window_plan(int64_t nodes, int width, int cus, fib::WindowPlan& p) {
+  double best = INFINITY;
+  for (int threads = 256; threads <= 1024; threads += 128) {
+    for (int S = 1; S <= 64; ++S) {
+      const int own = threads - 2 * S * width;
+      if (own < 16) break;
+      const int64_t blocks = (nodes + own - 1) / own;
+      const double per_cu = (double)((blocks + cus - 1) / cus);
+      const double cost = 1100.0 + 1000.0 * per_cu * ((threads + 255) / 256) + 6500.0 * per_cu / S;
+      if (cost < best) {
+        best = cost;
+        p = fib::WindowPlan{threads, S};
+      }
+    }
+  }
+  return best;
+}
+
+// Device data of the windowed diffusion (once; without memory for it the
+// partitioned solve stays).
+void window_setup(fib_ctx* c, bool steps) {
+  if (c->win.width == 0) return;
+  const size_t nt = (size_t)c->n_total;
+  bool ok = true;
+  if (!c->d_ends) {
+    int32_t* first = nullptr;
+    std::vector<int32_t> h(c->offsets.begin(), c->offsets.end());
+    ok = hipMalloc(&c->d_ends, sizeof(uint16_t) * nt) == hipSuccess &&
+         hipMalloc(&first, sizeof(int32_t) * h.size()) == hipSuccess &&
+         hipMemcpy(first, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice) ==
+             hipSuccess &&
+         fib::launch_node_ends(first, c->n_fibers, c->n_total, c->d_ends, c->stream) ==
+             hipSuccess &&
+         hipStreamSynchronize(c->stream) == hipSuccess;
+    (void)hipFree(first);
+  }
+  if (ok && !steps && !c->d_vmid) ok = hipMalloc(&c->d_vmid, sizeof(float) * nt) == hipSuccess;
+  if (ok && steps && !c->d_alt)
+    ok = hipMalloc(&c->d_alt, sizeof(float) * nt * c->S) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    c->win = fib::WindowStencil{};
+  }
+}
+
+// Windows at creation: contexts of the split schedule take the windowed
+// diffusion, or whole Hodgkin-Huxley steps on windows; schedule AUTO takes
+// the latter in place of the fused kernel where that leaves much of the chip
+// idle.  The fused kernel's cost by the same measure: 2100 cycles per step and
+// 980 for each node of a SIMD's threads (us per step, fused / windows: 1000
+// nodes 2.55 / 1.07, 36 083 2.56 / 1.43, 126 229 2.75 / 1.92, 419 886 5.40 / 4.43;
+// the 1369-fiber bundle 12.4 / 19.4).
+void window_create(fib_ctx* c) {
+  window_rule(c);
+  if (c->win.width == 0) return;
+  const bool hh_like = c->p.model == FIB_MODEL_HH || c->p.model == FIB_MODEL_HH_APX_EXP;
+  if (!hh_like) {
+    window_setup(c, false);
+    return;
+  }
+  const double cost = window_plan(c->n_total, c->win.width, c->cu_count, c->win_plan);
+  if (c->p.schedule == FIB_SCHED_AUTO) {
+    const bool automatic = c->p.threads_per_group == 0 && c->p.nodes_per_thread == 0 &&
+                           c->p.groups == 0 && c->p.tune == 0;
+    c->win_auto = automatic && cost < (c->threads + 255) / 256 * c->K * 980.0 + 2100.0;
+  }
+  if (c->win_auto || c->p.schedule == FIB_SCHED_SPLIT) window_setup(c, true);
 }
 
 int check_ctx(const fib_ctx* c) {
@@ -923,6 +1025,12 @@ int run_adaptive(fib_ctx* c, KArgs a, int64_t step0, int64_t n_steps) {
   HIP_TRY(hipMemcpyAsync(c->d_vprev, c->d_state, sizeof(float) * nt, hipMemcpyDeviceToDevice,
                          c->stream));
   const size_t lds = fib::lds_bytes_for(c->threads, c->levels);
+  const bool windowed = c->win.width > 0 && c->d_vmid;
+  if (windowed) a.v_out = c->d_vmid;
+  auto diffuse = [&]() {
+    return windowed ? fib::launch_diffuse_window(c->win, c->d_vmid, c->d_state, a, c->stream)
+                    : fib::launch_diffusion(c->K, c->groups, c->threads, lds, a, c->stream);
+  };
   // ST57: decisions, then the reaction parts over the list of solved nodes
   const bool listed = c->p.model == FIB_MODEL_ST57;
   int32_t* list = c->d_adapt_list;
@@ -951,17 +1059,18 @@ int run_adaptive(fib_ctx* c, KArgs a, int64_t step0, int64_t n_steps) {
     for (int64_t n = step0; n < end; ++n) {
       at(n);
       HIP_TRY(start(n, true, n > step0));
-      HIP_TRY(fib::launch_diffusion(c->K, c->groups, c->threads, lds, a, c->stream));
+      HIP_TRY(diffuse());
     }
     KArgs o = a;
     o.fiber_any = nullptr;
+    o.v_out = c->d_state;
     HIP_TRY(fib::launch_react(c->p.model, (int32_t)(end - 1), 0, 2, o, c->stream));
   } else {
     at(step0);
     HIP_TRY(start(step0, false, false));
     for (int64_t n = step0; n < end; ++n) {
       at(n);
-      HIP_TRY(fib::launch_diffusion(c->K, c->groups, c->threads, lds, a, c->stream));
+      HIP_TRY(diffuse());
       HIP_TRY(finish(n));
       if (n + 1 < end) {
         at(n + 1);
@@ -1120,9 +1229,19 @@ void graph_release(fib_ctx* c) {
 
 int surrogate_step(fib_ctx* c, const KArgs& a, int64_t n, hipStream_t stream);
 
-// Captures one block of P steps (relative steps 0 .. P-1) and replays it
-// `blocks` times from absolute step n0.
-int run_graph_blocks(fib_ctx* c, const KArgs& a, int64_t n0, int64_t P, int64_t blocks) {
+// Diffusion of the split schedule inside a run: windowed from the row the
+// reaction kernels left V_m in, else the partitioned solve in place.
+hipError_t diffuse_step(const fib_ctx* c, const KArgs& a, hipStream_t s) {
+  if (a.v_out != a.state) return fib::launch_diffuse_window(c->win, a.v_out, c->d_state, a, s);
+  return fib::launch_diffusion(c->K, c->groups, c->threads,
+                               fib::lds_bytes_for(c->threads, c->levels), a, s);
+}
+
+// Captures one block of P steps (relative steps 0 .. P-1), which `record`
+// launches, and replays it `blocks` times from absolute step n0.
+template <class Record>
+int run_graph_blocks(fib_ctx* c, const KArgs& a, int64_t n0, int64_t P, int64_t blocks,
+                     Record record) {
   graph_release(c);
   if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
   if (!c->graph_done) HIP_TRY(hipEventCreateWithFlags(&c->graph_done, hipEventDisableTiming));
@@ -1130,23 +1249,12 @@ int run_graph_blocks(fib_ctx* c, const KArgs& a, int64_t n0, int64_t P, int64_t 
     return fail(FIB_ENOMEM, "device allocation failed");
   KArgs g = a;
   g.step_base = c->d_step_base;
-  const size_t lds = fib::lds_bytes_for(c->threads, c->levels);
   const int slot0 = c->sur_slot, last0 = c->sur_last_slot;
   const int64_t steps0 = c->sur_steps;
   HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
+  int rc = record(g, c->cap_stream);
   hipError_t le = hipSuccess;
-  int rc = FIB_OK;
-  for (int64_t j = 0; j < P && le == hipSuccess && rc == FIB_OK; ++j) {
-    le = fib::launch_diffusion(c->K, c->groups, c->threads, lds, g, c->cap_stream);
-    if (le != hipSuccess) break;
-    const bool sample = g.samples && g.sample_every > 0 && (j + 1) % g.sample_every == 0;
-    if (c->sur_on && !sample)
-      rc = surrogate_step(c, g, j, c->cap_stream);
-    else
-      le = fib::launch_react(c->p.model, (int32_t)j, (int32_t)(j + 1), 1 | 2 | 4, g,
-                             c->cap_stream);
-  }
-  if (le == hipSuccess && rc == FIB_OK)
+  if (rc == FIB_OK)
     le = fib::launch_step_base(c->d_step_base, (int32_t)P, false, c->cap_stream);
   hipGraph_t graph = nullptr;
   const hipError_t ec = hipStreamEndCapture(c->cap_stream, &graph);
@@ -1179,6 +1287,57 @@ int run_graph_blocks(fib_ctx* c, const KArgs& a, int64_t n0, int64_t P, int64_t 
     ++c->graph_replays;
   }
   HIP_TRY(hipEventRecord(c->graph_done, c->stream));
+  return FIB_OK;
+}
+
+// fib_run on windows of whole steps (Hodgkin-Huxley): launches of up to
+// win_plan.steps steps that alternate between the two state buffers.  With
+// graphs (split schedule) whole blocks of P steps are one captured graph of an
+// even number of launches.  The last launch writes d_state: where the number
+// of launches comes out odd one more is made, or, for a single step, the state
+// is copied back.
+int run_windows(fib_ctx* c, const KArgs& a, int64_t step0, int64_t n_steps, int64_t P, int kt) {
+  float* buf[2] = {c->d_state, c->d_alt};
+  const int S = c->win_plan.steps, width = c->win.width;
+  const bool apx = c->p.model == FIB_MODEL_HH_APX_EXP;
+  int cur = 0;
+  // `count` steps from `n` in launches of an even (parity 0), odd (1) or any
+  // (-1) number where count allows it
+  auto segment = [&](const KArgs& g, int64_t n, int64_t count, int parity, hipStream_t s) -> int {
+    if (count <= 0) return FIB_OK;
+    int64_t m = (count + S - 1) / S;
+    if (parity >= 0 && (m & 1) != parity && m < count) ++m;
+    for (int64_t q = 0; q < m; ++q) {
+      const int steps = (int)(count / m + (q < count % m ? 1 : 0));
+      const int halo = steps * width;
+      const fib::WindowArgs wa{buf[cur], buf[cur ^ 1], c->win_plan.threads - 2 * halo, halo, steps};
+      if (s == c->stream)
+        KT_LAUNCH(c, kt, fib::launch_window_hh(apx, c->win, wa, c->win_plan, (int32_t)n, g, s));
+      else
+        HIP_TRY(fib::launch_window_hh(apx, c->win, wa, c->win_plan, (int32_t)n, g, s));
+      cur ^= 1;
+      n += steps;
+    }
+    return FIB_OK;
+  };
+  int64_t n = step0;
+  const int64_t end = step0 + n_steps;
+  const int64_t per_block = P > 0 ? (P + S - 1) / S : 0;
+  if (per_block % 2 == 0 ? P > 0 : per_block < P) {  // an even number of launches is possible
+    const int64_t pre = std::min((P - n % P) % P, n_steps);
+    const int64_t blocks = (end - 1 - n - pre) / P;
+    if (blocks > 0) {
+      if (int rc = segment(a, n, pre, -1, c->stream)) return rc;
+      n += pre;
+      auto block = [&](const KArgs& g, hipStream_t s) { return segment(g, 0, P, 0, s); };
+      if (int rc = run_graph_blocks(c, a, n, P, blocks, block)) return rc;
+      n += blocks * P;
+    }
+  }
+  if (int rc = segment(a, n, end - n, cur, c->stream)) return rc;
+  if (cur != 0)
+    HIP_TRY(hipMemcpyAsync(buf[0], buf[1], sizeof(float) * c->n_total * c->S,
+                           hipMemcpyDeviceToDevice, c->stream));
   return FIB_OK;
 }
 
@@ -1343,6 +1502,7 @@ int fib_create(const fib_params* p, int32_t n_fibers, const int32_t* n_nodes, vo
   if (fib::launch_fill(c->d_tact, total, INFINITY, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return bail(fail(FIB_EHIP, "device initialization failed"));
+  window_create(c);
   *out = c;
   return FIB_OK;
 }
@@ -1359,6 +1519,9 @@ void fib_destroy(fib_t* c) {
   (void)hipFree(c->d_bin_ent);
   (void)hipFree(c->d_node_stim);
   (void)hipFree(c->d_stim);
+  (void)hipFree(c->d_ends);
+  (void)hipFree(c->d_vmid);
+  (void)hipFree(c->d_alt);
   (void)hipFree(c->d_sur_frags);
   (void)hipFree(c->d_sur_bias);
   (void)hipFree(c->d_sur_tab);
@@ -1647,6 +1810,10 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
   const bool hh_like = c->p.model == FIB_MODEL_HH || c->p.model == FIB_MODEL_HH_APX_EXP;
   const bool fused = c->p.schedule == FIB_SCHED_FUSED ||
                      (c->p.schedule == FIB_SCHED_AUTO && hh_like && !c->sur_on);
+  if (hh_like && !c->sur_on && c->win.width > 0 && c->d_alt &&
+      (c->p.schedule == FIB_SCHED_SPLIT || (fused && c->win_auto && !c->tuned)))
+    return run_windows(c, a, step0, n_steps, fused ? 0 : graph_period(c, a),
+                       fused ? FIB_KT_FUSED : FIB_KT_REACTION);
   if (fused) {
     if (!hh_like)
       return fail(FIB_EUNSUPPORTED, "the fused schedule holds Hodgkin-Huxley states only");
@@ -1657,8 +1824,11 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
   }
   HIP_TRY(hipMemcpyAsync(c->d_vprev, c->d_state, sizeof(float) * c->n_total,
                          hipMemcpyDeviceToDevice, c->stream));
-  const size_t lds = fib::lds_bytes_for(c->threads, c->levels);
   const int64_t end = step0 + n_steps;
+  // launches that end a run leave V_m in the state, those a diffusion follows
+  // where it reads it
+  const KArgs fin = a;
+  if (c->win.width > 0 && c->d_vmid) a.v_out = c->d_vmid;
   if (godunov) {
     // SPLIT, Godunov: per split step one reaction launch (observables of
     // step n-1, then step n's prescriptions and its whole reaction) and one
@@ -1667,11 +1837,10 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
       const int flags = (n > step0 ? 2 : 0) | 4;
       KT_LAUNCH(c, FIB_KT_REACTION,
                 fib::launch_react(c->p.model, (int32_t)(n - 1), (int32_t)n, flags, a, c->stream));
-      KT_LAUNCH(c, FIB_KT_DIFFUSION,
-                fib::launch_diffusion(c->K, c->groups, c->threads, lds, a, c->stream));
+      KT_LAUNCH(c, FIB_KT_DIFFUSION, diffuse_step(c, a, c->stream));
     }
     KT_LAUNCH(c, FIB_KT_REACTION,
-              fib::launch_react(c->p.model, (int32_t)(end - 1), 0, 2, a, c->stream));
+              fib::launch_react(c->p.model, (int32_t)(end - 1), 0, 2, fin, c->stream));
     return FIB_OK;
   }
   // SPLIT, Strang: per split step one diffusion launch and one reaction
@@ -1679,8 +1848,7 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
   // n+1 (prescriptions, first half); whole blocks of steps as graph replays
   KT_LAUNCH(c, FIB_KT_REACTION, fib::launch_react(c->p.model, 0, (int32_t)step0, 4, a, c->stream));
   auto eager = [&](int64_t n) -> int {
-    KT_LAUNCH(c, FIB_KT_DIFFUSION,
-              fib::launch_diffusion(c->K, c->groups, c->threads, lds, a, c->stream));
+    KT_LAUNCH(c, FIB_KT_DIFFUSION, diffuse_step(c, a, c->stream));
     const bool last = n + 1 >= end;
     const bool sample = a.samples && a.sample_every > 0 && (n + 1) % a.sample_every == 0;
     if (c->sur_on && !last && !sample) {
@@ -1688,7 +1856,8 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
     } else {
       const int flags = 1 | 2 | (last ? 0 : 4);
       KT_LAUNCH(c, FIB_KT_REACTION,
-                fib::launch_react(c->p.model, (int32_t)n, (int32_t)(n + 1), flags, a, c->stream));
+                fib::launch_react(c->p.model, (int32_t)n, (int32_t)(n + 1), flags, last ? fin : a,
+                                  c->stream));
     }
     return FIB_OK;
   };
@@ -1700,7 +1869,19 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
     // whole blocks, none of which holds the last step of the call
     const int64_t blocks = n < end ? (end - 1 - n) / P : 0;
     if (blocks > 0) {
-      if (int rc = run_graph_blocks(c, a, n, P, blocks)) return rc;
+      auto block = [&](const KArgs& g, hipStream_t s) -> int {
+        for (int64_t j = 0; j < P; ++j) {
+          HIP_TRY(diffuse_step(c, g, s));
+          const bool sample = g.samples && g.sample_every > 0 && (j + 1) % g.sample_every == 0;
+          if (c->sur_on && !sample) {
+            if (int rc = surrogate_step(c, g, j, s)) return rc;
+          } else {
+            HIP_TRY(fib::launch_react(c->p.model, (int32_t)j, (int32_t)(j + 1), 1 | 2 | 4, g, s));
+          }
+        }
+        return FIB_OK;
+      };
+      if (int rc = run_graph_blocks(c, a, n, P, blocks, block)) return rc;
       n += blocks * P;
     }
   }
@@ -1715,8 +1896,11 @@ int fib_autotune(fib_t* c, int32_t trial_steps, int32_t max_candidates, double* 
   if (int rc = check_ctx(c)) return rc;
   // the trials time the plain schedule; the adaptive flags stay untouched
   const double tol = c->adapt_tol;
+  const bool tuned = c->tuned;
   c->adapt_tol = 0.0;
+  c->tuned = true;  // the shapes are the whole-fiber kernels'
   const int rc = autotune_impl(c, trial_steps, max_candidates, ms_per_step);
+  if (rc) c->tuned = tuned;
   c->adapt_tol = tol;
   return rc;
 }
@@ -1821,7 +2005,6 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
   }
   if (copy_all(false) != hipSuccess && !rc) rc = fail(FIB_EHIP, "autotune: state copy failed");
   cleanup();
-  if (!rc) c->tuned = true;
   if (!rc && ms_per_step) *ms_per_step = best / trial_steps;
   return rc;
 }
@@ -1905,6 +2088,7 @@ int fib_set_surrogate(fib_t* c, const fib_mlp_t* net, const float* in_shift, con
   // both rejection counters start at zero; each surrogate step clears the
   // one the next step uses
   if (int rc = surrogate_buffers(c)) return rc;
+  window_setup(c, false);
   HIP_TRY(hipMemcpy(c->d_sur_tab, tab.data(), sizeof(float) * tab.size(), hipMemcpyHostToDevice));
   HIP_TRY(fib::launch_pack(sn, fib::mlp_device_params(net), c->d_sur_frags, c->d_sur_bias, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1940,6 +2124,7 @@ int fib_set_predictor(fib_t* c, int32_t predictor, const float* res_scale, doubl
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->sur_on = false;
   if (int rc = surrogate_buffers(c)) return rc;
+  window_setup(c, false);
   HIP_TRY(hipMemcpy(c->d_sur_tab, tab.data(), sizeof(float) * tab.size(), hipMemcpyHostToDevice));
   c->sur_grid = c->cu_count * 8;
   c->sur_pred = predictor;
@@ -2089,6 +2274,7 @@ int fib_set_adaptive(fib_t* c, double tol) {
     }
   }
   if (int rc = adapt_plan(c, true)) return rc;
+  window_setup(c, false);
   if (c->n_fibers > 0)
     HIP_TRY(hipMemcpy(c->d_first_on, c->first_on.data(), sizeof(int32_t) * c->n_fibers,
                       hipMemcpyHostToDevice));

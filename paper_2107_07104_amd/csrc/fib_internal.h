@@ -101,6 +101,9 @@ struct KArgs {
   const int32_t* ent_fiber; // the entry's fiber
   int32_t max_ents;         // the most entries of one bin (end entry included)
   int32_t n_bins;           // bins (workgroups of the fused kernels)
+  const uint16_t* node_ends;// [n_total] distances to the fiber's ends, clipped: dl | dr << 8
+  float* v_out;             // row the reaction kernels write V_m to (state row 0, or the
+                            // row the windowed diffusion reads)
   float rest[MAX_STATES];   // resting state (FP32); device rows hold y_k - rest[k]
 };
 
@@ -220,6 +223,34 @@ __device__ __forceinline__ int32_t step_base_of(const KArgs& a) {
   return a.step_base ? *a.step_base : 0;
 }
 hipError_t launch_check_finite(const float* p, int64_t n, int* flag, hipStream_t s);
+
+// Windowed diffusion (window_kernels.hip): its weights, one per distance,
+// and the width the kernels are built for.
+constexpr int kMaxWidth = 32;
+struct WindowStencil {
+  int width;
+  float h[kMaxWidth];
+};
+// Stencil of one substep with row weight w = theta c dt / h^2 of the matrix;
+// false where it is wider than the kernels are built for.
+bool window_stencil(double w, double theta, WindowStencil& st);
+// Whole split steps on windows: threads per block and steps per launch, and
+// one launch's arguments (state rows in -> out, nodes a block owns, nodes it
+// computes beyond them at either side, steps).
+struct WindowPlan {
+  int threads, steps;
+};
+struct WindowArgs {
+  const float* in;
+  float* out;
+  int own, halo, steps;
+};
+hipError_t launch_node_ends(const int32_t* first, int n_fibers, int64_t nt, uint16_t* ends,
+                            hipStream_t s);
+hipError_t launch_diffuse_window(const WindowStencil& st, const float* in, float* out,
+                                 const KArgs& a, hipStream_t s);
+hipError_t launch_window_hh(bool apx, const WindowStencil& st, const WindowArgs& wa,
+                            const WindowPlan& p, int32_t step0, const KArgs& a, hipStream_t s);
 
 // LDS bytes the fused / diffusion kernels need for `threads` threads and
 // `levels` PCR levels.

@@ -1067,8 +1067,9 @@ __global__ __launch_bounds__(256) void k_react(KArgs A, int32_t step_a, int32_t 
 #pragma unroll
   for (int k = 0; k < M::S; ++k) u[k] = A.state[k * nt + i];
   react_node<M>(A, i, u, step_a, step_b, flags);
+  A.v_out[i] = u[0];
 #pragma unroll
-  for (int k = 0; k < M::S; ++k) A.state[k * nt + i] = u[k];
+  for (int k = 1; k < M::S; ++k) A.state[k * nt + i] = u[k];
 }
 
 // The same phases over a grid that fits on the device at once: a thread
@@ -1126,8 +1127,9 @@ __global__ __launch_bounds__(256) void k_react_stream(KArgs A, int32_t step_a, i
       if (set_b) u[0] = vb;
       for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, Ib, A.tau, A.inv_cm);
     }
+    A.v_out[i] = u[0];
 #pragma unroll
-    for (int k = 0; k < M::S; ++k) A.state[k * nt + i] = u[k];
+    for (int k = 1; k < M::S; ++k) A.state[k * nt + i] = u[k];
   }
 }
 
@@ -1180,9 +1182,10 @@ __global__ __launch_bounds__(256) void k_adapt_start(KArgs A, int32_t step, int 
   const uint64_t mask = __ballot(solve);
   if ((threadIdx.x & 63) == 0 && mask)
     atomicAdd(&A.adapt_count[blockIdx.x % kAdaptCounters], (unsigned long long)__popcll(mask));
-  if (!real || !on) return;
+  if (!real) return;
   if (!solve) {
-    A.pt_cur[i] = 0;
+    if (A.v_out != A.state) A.v_out[i] = A.state[i];
+    if (on) A.pt_cur[i] = 0;
     return;
   }
   A.fiber_any[f] = 1;
@@ -1201,8 +1204,9 @@ __global__ __launch_bounds__(256) void k_adapt_start(KArgs A, int32_t step, int 
     for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
     A.pt_cur[i] = PT_SOLVE;
   }
+  A.v_out[i] = u[0];
 #pragma unroll
-  for (int k = 0; k < S; ++k) A.state[k * nt + i] = u[k];
+  for (int k = 1; k < S; ++k) A.state[k * nt + i] = u[k];
 }
 
 // End of Strang split step `step`: second reaction half and equilibrium
@@ -1261,6 +1265,8 @@ __global__ __launch_bounds__(256) void k_adapt_decide(KArgs A, int32_t step, int
     base = __shfl(base, first);
     if (solve) list[base + __popcll(mask & ((1ull << lane) - 1ull))] = (int)i;
   }
+  // V of every node where the diffusion reads it; solved nodes replace theirs
+  if (real && A.v_out != A.state) A.v_out[i] = A.state[i];
   if (!real || !on) return;
   if (!solve) {
     A.pt_cur[i] = 0;
@@ -1305,8 +1311,9 @@ __global__ __launch_bounds__(256) void k_adapt_solve(KArgs A, int32_t step,
         for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
       }
     }
+    (PHASE == 1 ? A.state : A.v_out)[i] = u[0];
 #pragma unroll
-    for (int k = 0; k < S; ++k) A.state[k * nt + i] = u[k];
+    for (int k = 1; k < S; ++k) A.state[k * nt + i] = u[k];
   }
 }
 

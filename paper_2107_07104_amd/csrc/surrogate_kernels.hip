@@ -476,9 +476,10 @@ __global__ __launch_bounds__(64 * WAVES) void k_surrogate(
         }
         const float2 ob = obs[lane];
         observe_with(A, i, step_a, fmaf(0.5f * span, G[0], u[0]), ob.x, ob.y, *uth_lds);
-        Column col{A.state + i, nt};
+        ((gfloat*)A.v_out)[i] = fmaf(span, G[0], u[0]);
+        Column col{A.state + nt + i, nt};
 #pragma unroll
-        for (int k = 0; k < S; ++k) {
+        for (int k = 1; k < S; ++k) {
           col.p[0] = fmaf(span, G[k], u[k]);
           col.next();
         }
@@ -599,8 +600,9 @@ __global__ __launch_bounds__(256, 2) void k_midpoint(KArgs A, const float* __res
         A.t_act[i] = fmaf(A.dt, (uth - v0) / (v1 - v0), (float)step_a * A.dt);
       A.v_prev[i] = v1;
       if (!isfinite(v1)) atomicOr(A.flag, 1);
+      A.v_out[i] = fmaf(span, G[0], u[0]);
 #pragma unroll
-      for (int k = 0; k < S; ++k) A.state[k * nt + i] = fmaf(span, G[k], u[k]);
+      for (int k = 1; k < S; ++k) A.state[k * nt + i] = fmaf(span, G[k], u[k]);
     }
     const bool reject = real && !ok;
     const uint64_t mask = __ballot(reject);
@@ -640,8 +642,9 @@ __global__ __launch_bounds__(256) void k_fallback(KArgs A, const int* __restrict
     float Ib, vp;
     if (stim_eval(sid, A.stim, step_a + 1, Ib, vp)) u[0] = vp;
     for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, Ib, A.tau, A.inv_cm);
+    A.v_out[i] = u[0];
 #pragma unroll
-    for (int k = 0; k < S; ++k) A.state[k * nt + i] = u[k];
+    for (int k = 1; k < S; ++k) A.state[k * nt + i] = u[k];
   }
 }
 
