@@ -292,6 +292,7 @@ struct fib_ctx {
   // (Hodgkin-Huxley) the second buffer of states and the plan
   fib::WindowStencil win{};
   uint16_t* d_ends = nullptr;
+  int32_t* d_first = nullptr;  // the fibers' first nodes, then n_total
   float* d_vmid = nullptr;
   float* d_alt = nullptr;
   fib::WindowPlan win_plan{};
@@ -787,16 +788,14 @@ void window_setup(fib_ctx* c, bool steps) {
   const size_t nt = (size_t)c->n_total;
   bool ok = true;
   if (!c->d_ends) {
-    int32_t* first = nullptr;
     std::vector<int32_t> h(c->offsets.begin(), c->offsets.end());
     ok = hipMalloc(&c->d_ends, sizeof(uint16_t) * nt) == hipSuccess &&
-         hipMalloc(&first, sizeof(int32_t) * h.size()) == hipSuccess &&
-         hipMemcpy(first, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice) ==
+         hipMalloc(&c->d_first, sizeof(int32_t) * h.size()) == hipSuccess &&
+         hipMemcpy(c->d_first, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice) ==
              hipSuccess &&
-         fib::launch_node_ends(first, c->n_fibers, c->n_total, c->d_ends, c->stream) ==
+         fib::launch_node_ends(c->d_first, c->n_fibers, c->n_total, c->d_ends, c->stream) ==
              hipSuccess &&
          hipStreamSynchronize(c->stream) == hipSuccess;
-    (void)hipFree(first);
   }
   if (ok && !steps && !c->d_vmid) ok = hipMalloc(&c->d_vmid, sizeof(float) * nt) == hipSuccess;
   if (ok && steps && !c->d_alt)
@@ -1021,6 +1020,17 @@ int run_adaptive(fib_ctx* c, KArgs a, int64_t step0, int64_t n_steps) {
     a.fiber_any_next = c->d_fiber_any + ((n + 1) & 1) * nf;
   };
   if (int rc = adapt_align_flags(c, step0)) return rc;
+  const int32_t longest = *std::max_element(c->n_nodes.begin(), c->n_nodes.end());
+  if (c->p.model == FIB_MODEL_ST57 && c->win.width > 0 && c->d_first &&
+      fib::adapt_fiber_fits(longest, nt, c->max_lds)) {
+    // one launch, a fiber per workgroup
+    a.pt_prev = c->d_pt + ((step0 + 1) & 1) * nt;
+    a.pt_cur = c->d_pt + ((end - 1) & 1) * nt;
+    HIP_TRY(fib::launch_run_st57_adapt(godunov, c->win, c->d_first, c->n_fibers, longest,
+                                       c->cu_count, a, c->stream));
+    c->adapt_par = (int)((end - 1) & 1);
+    return FIB_OK;
+  }
   HIP_TRY(hipMemsetAsync(c->d_fiber_any, 0, 2 * (size_t)nf, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d_vprev, c->d_state, sizeof(float) * nt, hipMemcpyDeviceToDevice,
                          c->stream));
@@ -1520,6 +1530,7 @@ void fib_destroy(fib_t* c) {
   (void)hipFree(c->d_node_stim);
   (void)hipFree(c->d_stim);
   (void)hipFree(c->d_ends);
+  (void)hipFree(c->d_first);
   (void)hipFree(c->d_vmid);
   (void)hipFree(c->d_alt);
   (void)hipFree(c->d_sur_frags);

@@ -25,6 +25,7 @@
 
 #include "fib_internal.h"
 #include "hh_model.h"
+#include "st57_model.h"
 
 namespace fib {
 
@@ -83,9 +84,9 @@ __global__ __launch_bounds__(256) void k_node_ends(const int32_t* __restrict__ f
 // whose 4 + 2 W neighbours it then holds in registers.  With adaptive
 // computation (fiber_any) fibers without a solved node keep V, and every
 // fiber's flag of the step after next is cleared by its first node.  Bound by
-// HBM (8 B per node): 4e6 nodes in DIFF4 us, 2e7 in DIFF20; one node per
-// thread, with its 2 W reads from LDS, took 21 us for 4e6, the partitioned
-// solve in its place (six barriers per bin of one fiber) 15 us.
+// HBM (8 B per node): 4e6 nodes in 14.5 us; one node per thread, with its
+// 2 W reads from LDS, took 21 us, the partitioned solve in its place (six
+// barriers per bin of one fiber) 15 us.
 constexpr int kDiffNodes = 1024;
 
 template <int W>
@@ -243,6 +244,240 @@ __global__ __launch_bounds__(1024) void k_window_hh(KArgs A, WindowStencil st, W
 }
 
 // ---------------------------------------------------------------------------
+// Adaptive computation of the 57-state model, a fiber per workgroup
+// ---------------------------------------------------------------------------
+
+// LDS of k_run_st57_adapt for a fiber of n nodes (bytes): V_m twice with the
+// stencil's padding, V_m at the end of the previous step, the list of solved
+// nodes, the verdicts of two steps; then kStimCache stimulus entries, two
+// list lengths and the range of the fiber's entries.
+constexpr int kStimCache = 8;
+__host__ __device__ inline int adapt_v_row(int n) { return n + 2 * kMaxWidth; }
+__host__ __device__ inline size_t adapt_fiber_lds(int n) {
+  const size_t rows = sizeof(float) * (2 * (size_t)adapt_v_row(n) + n) + 4 * (size_t)n;
+  return (rows + 15) / 16 * 16 + kStimCache * sizeof(StimDev) + 4 * sizeof(int32_t);
+}
+
+// Split steps step0 .. step0 + n_steps - 1 of one fiber per workgroup with the
+// adaptive computation's rules (k_adapt_decide / k_adapt_solve, which take a
+// launch for each part): V_m, the verdicts and the list of solved nodes stay in
+// LDS; the other states are read from and written to memory for solved nodes
+// only.  Per step:
+//   1. each node is solved if the last check found it or a neighbour active
+//      or a stimulus entry that is on covers one of them; the solved nodes go
+//      to a list (before the fiber's first stimulus none);
+//   2. the first reaction part over the list (Godunov: the only part, with
+//      the check);
+//   3. the windowed diffusion of the whole fiber;
+//   4. Strang: the second half and the check, on the states still in registers
+//      where the list fits one round;
+//   5. the observables.
+// A step without a solved node skips 2 to 4.
+//
+// Bound by the reaction's chain (six right-hand sides per half, 6-7 us) on the
+// few waves the solved nodes fill; the four launches it replaces took 65 us
+// per step on 400 x 1481 nodes with 6 % firing (22 of them reading flags), this
+// 33.  Fibers are independent, so no other synchronization is needed;
+// with more fibers than compute units workgroups of four waves run two to a
+// unit, else of eight.
+template <bool GODUNOV, int W>
+__global__ __launch_bounds__(512, 2) void k_run_st57_adapt(KArgs A, WindowStencil st,
+                                                           const int32_t* __restrict__ first) {
+  constexpr int S = st57::S;
+  extern __shared__ __align__(16) char smem[];
+  const int f = blockIdx.x, t = threadIdx.x, T = blockDim.x, lane = t & 63;
+  const int64_t off = first[f], nt = A.n_total;
+  const int N = first[f + 1] - first[f];
+  const int vrow = adapt_v_row(N);
+  float* v_in = reinterpret_cast<float*>(smem) + kMaxWidth;  // node i at [i]
+  float* v_new = v_in + vrow;
+  float* v_prev = reinterpret_cast<float*>(smem) + 2 * vrow;
+  uint16_t* list = reinterpret_cast<uint16_t*>(v_prev + N);
+  uint8_t* act[2] = {reinterpret_cast<uint8_t*>(list + N),
+                     reinterpret_cast<uint8_t*>(list + N) + N};
+  char* tail = smem + adapt_fiber_lds(N) - kStimCache * sizeof(StimDev) - 4 * sizeof(int32_t);
+  StimDev* cache = reinterpret_cast<StimDev*>(tail);
+  int32_t* cnt = reinterpret_cast<int32_t*>(tail + kStimCache * sizeof(StimDev));
+  int32_t* sid_lo = cnt + 2;  // smallest and largest entry + 1 of the fiber
+  int32_t* sid_hi = cnt + 3;
+
+  if (t == 0) {
+    cnt[0] = cnt[1] = 0;
+    *sid_lo = INT32_MAX;
+    *sid_hi = 0;
+  }
+  for (int p = t; p < kMaxWidth; p += T) {
+    v_in[-1 - p] = v_new[-1 - p] = 0.0f;
+    v_in[N + p] = v_new[N + p] = 0.0f;
+  }
+  __syncthreads();
+  // bit j of a mask: node t + j T
+  uint32_t watch = 0, stim = 0;
+  for (int j = 0, i = t; i < N; ++j, i += T) {
+    const float v = A.state[off + i];
+    v_in[i] = v;
+    v_prev[i] = v;
+    act[0][i] = (A.pt_prev[off + i] & PT_ACTIVE) ? 1 : 0;
+    if (isinf(A.t_act[off + i])) watch |= 1u << j;
+    // the node's own entry or a neighbour's
+    const int32_t s0 = A.node_stim[off + i];
+    const int32_t sl = i > 0 ? A.node_stim[off + i - 1] : 0;
+    const int32_t sr = i + 1 < N ? A.node_stim[off + i + 1] : 0;
+    if (s0 | sl | sr) stim |= 1u << j;
+    if (s0) {
+      atomicMin(sid_lo, s0);
+      atomicMax(sid_hi, s0);
+    }
+  }
+  __syncthreads();
+  const int32_t lo = *sid_lo, n_ent = *sid_hi - lo + 1;
+  const bool cached = *sid_hi > 0 && n_ent <= kStimCache;
+  if (cached && t < n_ent) cache[t] = A.stim[lo - 1 + t];
+  __syncthreads();
+  auto entry = [&](int32_t sid) { return cached ? cache[sid - lo] : A.stim[sid - 1]; };
+  auto on_at = [&](int i, int32_t n) {
+    const int32_t sid = A.node_stim[off + i];
+    return sid != 0 && stim_on(entry(sid), n);
+  };
+  const int32_t first_on = A.fiber_first_on[f];
+
+  unsigned long long solved = 0;
+  const int32_t n_end = A.step0 + A.n_steps;
+  int par = 0;
+  for (int32_t n = A.step0; n < n_end; ++n, par ^= 1) {
+    // 1. nodes to solve; verdicts of the others
+    const bool on = n >= first_on;
+    if (on) {
+      const uint8_t* a = act[par];
+      for (int j = 0, i0 = t - lane; i0 < N; ++j, i0 += T) {
+        const int i = i0 + lane;
+        bool solve = false;
+        if (i < N) {
+          const int il = i > 0 ? i - 1 : i, ir = i + 1 < N ? i + 1 : i;
+          solve = (a[i] | a[il] | a[ir]) != 0;
+          if (!solve && ((stim >> j) & 1u)) solve = on_at(i, n) || on_at(il, n) || on_at(ir, n);
+          if (!solve) act[par ^ 1][i] = 0;
+        }
+        const uint64_t mask = __ballot(solve);
+        if (mask) {
+          int base = 0;
+          if (lane == 0) base = atomicAdd(&cnt[par], __popcll(mask));
+          base = __builtin_amdgcn_readfirstlane(base);
+          if (solve) list[base + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)i;
+        }
+      }
+    } else {
+      for (int i = t; i < N; i += T) act[par ^ 1][i] = act[par][i];
+    }
+    if (t == 0) cnt[par ^ 1] = 0;
+    __syncthreads();
+    const int c = cnt[par];
+    if (c) {
+      solved += t == 0 ? (unsigned)c : 0u;
+      float u[S];
+      float I = 0.0f;
+      // whether the state moved over a reaction part from V offset vb and the
+      // other states still in memory
+      auto moved = [&](int64_t g, float vb) {
+        gfloat* col = (gfloat*)(A.state + g);
+        __asm__("" : "+v"(col));  // read again, not kept through the substeps
+        bool m = fabsf(u[0] - vb) > A.adapt_tol * fabsf(vb + A.rest[0]);
+#pragma unroll
+        for (int k = 1; k < S; ++k) {
+          const float b = col[k * nt];
+          m |= fabsf(u[k] - b) > A.adapt_tol * fabsf(b + A.rest[k]);
+        }
+        return m;
+      };
+      // 2. first part
+      for (int e = t; e < c; e += T) {
+        const int i = list[e];
+        const int64_t g = off + i;
+#pragma unroll
+        for (int k = 1; k < S; ++k) u[k] = A.state[k * nt + g];
+        u[0] = v_in[i];
+        I = 0.0f;
+        const int32_t sid = A.node_stim[g];
+        if (sid) {
+          const StimDev en = entry(sid);
+          if (stim_on(en, n)) {
+            if (en.voltage) u[0] = en.amp;
+            else I = en.amp;
+          }
+        }
+        const float vb = u[0];
+        for (int s = 0; s < A.n_sub; ++s) st57::heun(u, A.rest, I, A.tau, A.inv_cm);
+        if (GODUNOV) act[par ^ 1][i] = moved(g, vb) ? 1 : 0;
+        v_in[i] = u[0];
+#pragma unroll
+        for (int k = 1; k < S; ++k) A.state[k * nt + g] = u[k];
+      }
+      __syncthreads();
+      // 3. diffusion
+      for (int i0 = t - lane; i0 < N; i0 += T) {
+        const int i = i0 + lane < N ? i0 + lane : N - 1;
+        const float v = window_diffuse<W>(v_in + i, v_in[i], i, N - 1 - i, st);
+        if (i0 + lane < N) v_new[i] = v;
+      }
+      __syncthreads();
+      float* sw = v_in;
+      v_in = v_new;
+      v_new = sw;
+      // 4. second half and the check
+      if (!GODUNOV) {
+        for (int e = t; e < c; e += T) {
+          const int i = list[e];
+          const int64_t g = off + i;
+          if (c > T) {
+#pragma unroll
+            for (int k = 1; k < S; ++k) u[k] = A.state[k * nt + g];
+            const int32_t sid = A.node_stim[g];
+            I = 0.0f;
+            if (sid) {
+              const StimDev en = entry(sid);
+              if (!en.voltage && stim_on(en, n)) I = en.amp;
+            }
+          }
+          const float vb = v_in[i];
+          u[0] = vb;
+          for (int s = 0; s < A.n_sub; ++s) st57::heun(u, A.rest, I, A.tau, A.inv_cm);
+          act[par ^ 1][i] = moved(g, vb) ? 1 : 0;
+          v_in[i] = u[0];
+#pragma unroll
+          for (int k = 1; k < S; ++k) A.state[k * nt + g] = u[k];
+        }
+        __syncthreads();
+      }
+    }
+    // 5. observables of this thread's nodes
+    const bool sample = A.sample_every > 0 && ((int64_t)n + 1) % A.sample_every == 0;
+    if (c || sample) {
+      const float uth = A.v_th - A.rest[0];
+      const int64_t r = sample ? ((int64_t)n + 1) / A.sample_every - 1 - A.sample_row0 : 0;
+      for (int j = 0, i = t; i < N; ++j, i += T) {
+        const float v0 = v_prev[i], v1 = v_in[i];
+        if (((watch >> j) & 1u) && v0 < uth && v1 >= uth) {
+          A.t_act[off + i] = fmaf(A.dt, (uth - v0) / (v1 - v0), (float)n * A.dt);
+          watch &= ~(1u << j);
+        }
+        if (sample) A.samples[r * nt + off + i] = v1 + A.rest[0];
+        v_prev[i] = v1;
+      }
+    }
+  }
+  __syncthreads();
+  bool bad = false;
+  for (int i = t; i < N; i += T) {
+    const float v = v_in[i];
+    A.state[off + i] = v;
+    A.pt_cur[off + i] = act[par][i] ? PT_ACTIVE : 0;
+    bad |= !isfinite(v);
+  }
+  if (bad) atomicOr(A.flag, 1);
+  if (solved) atomicAdd(&A.adapt_count[f % kAdaptCounters], solved);
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 
@@ -285,6 +520,34 @@ hipError_t launch_diffuse_window(const WindowStencil& st, const float* in, float
   const dim3 grid((unsigned)((a.n_total + kDiffNodes - 1) / kDiffNodes)), block(256);
 #define FIB_LAUNCH(W) \
   if (st.width == W) hipLaunchKernelGGL(k_diffuse_window<W>, grid, block, 0, s, a, st, in, out);
+  FIB_FOR_EACH_WIDTH(FIB_LAUNCH)
+#undef FIB_LAUNCH
+  return hipGetLastError();
+}
+
+// A thread's masks hold 32 nodes.  The chip takes 131072 nodes a round, a
+// fiber's workgroup 512, and a round of either is about 40 us a step (two
+// waves per SIMD); the launches cost 65 us, the workgroup 12.  So the
+// workgroup is not behind, with up to half the longest fiber solved, while
+// its rounds are at most one more than the chip's.
+bool adapt_fiber_fits(int n, int64_t nt, size_t lds) {
+  return n <= 32 * 256 && (n + 1023) / 1024 <= 1 + (nt + 131071) / 131072 &&
+         adapt_fiber_lds(n) <= lds;
+}
+
+hipError_t launch_run_st57_adapt(bool godunov, const WindowStencil& st, const int32_t* first,
+                                 int n_fibers, int max_nodes, int cus, const KArgs& a,
+                                 hipStream_t s) {
+  if (a.n_total == 0) return hipSuccess;
+  const dim3 grid((unsigned)n_fibers), block(n_fibers > cus ? 256 : 512);
+  const size_t lds = adapt_fiber_lds(max_nodes);
+#define FIB_LAUNCH(W)                                                                          \
+  if (st.width == W) {                                                                         \
+    if (godunov)                                                                               \
+      hipLaunchKernelGGL((k_run_st57_adapt<true, W>), grid, block, lds, s, a, st, first);      \
+    else                                                                                       \
+      hipLaunchKernelGGL((k_run_st57_adapt<false, W>), grid, block, lds, s, a, st, first);     \
+  }
   FIB_FOR_EACH_WIDTH(FIB_LAUNCH)
 #undef FIB_LAUNCH
   return hipGetLastError();
