@@ -5,12 +5,33 @@
 Every HIP source is compiled with packed FP32 arithmetic disabled
 (-packed-fp32-ops); the host side of hipcc warns that it does not know that
 target feature, which is harmless.
+
+Paced kernels (FIB_PACED in fib_internal.h) get an `s_nop 0` after every
+PACE vector instructions of a long basic block.  A wave that issues
+an exp, log or rcp holds its SIMD to one vector instruction per 4.2 to 4.7
+clocks for the next hundred or so, with any number of waves; an instruction
+that leaves the vector pipe lets the SIMD go to another wave, and two waves or
+more together then reach one per 3 clocks.  A wave alone on its SIMD only pays
+for the s_nop (12 %).  Clocks of a Heun step of the 57-state model per SIMD,
+and of 9 nodes of Hodgkin-Huxley:
+
+    s_nop after every          none     3     4     5     6     7     8    12    16
+    57 states, two waves       8033  6766  6532  6488  6446  6496  6529  6636  6739
+    57 states, one wave        4497  5702  5374  5235  5054  5015  4943  4784  4695
+    Hodgkin-Huxley, 2 waves     875   761   757   752   758   759   779   788   808
+
+The s_nop cannot be put there from the source: the scheduler moves the vector
+instructions past it, and most end up next to each other.  So a source with
+paced kernels is compiled to assembly, spaced there, and assembled.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
+import re
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.dirname(HERE)
@@ -20,23 +41,118 @@ SOURCES = ["fib_api.hip", "fib_kernels.hip", "mlp_api.hip", "mlp_kernels.hip",
            "surrogate_kernels.hip", "window_kernels.hip",
            "emg.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LLVM = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "llvm", "bin")
 ARCH = "gfx950"
+PACE = 6          # vector instructions between two s_nop
+PACE_BLOCK = 48   # of a basic block that is spaced, at least
+MARK = "; fib paced"
 
 FLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function",
+    "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
     "-I", os.path.join(ROOT, "include"),
 ]
 
+_VALU = re.compile(r"\s+v_(?!nop)")
+_OTHER = re.compile(r"\s+(s_|ds_|global_|buffer_|flat_|scratch_)")
+_ENDS = re.compile(r"\s+s_(c?branch|endpgm|setpc|swappc)")
+
+
+def _space(block: list[str]) -> list[str]:
+    """A basic block's lines with an s_nop after every PACE vector
+    instructions in a row.  Only lines that hold a vector instruction are
+    followed by one, so pairs that the assembler reads together (s_getpc and
+    the additions to it) stay together."""
+    if sum(1 for l in block if _VALU.match(l)) < PACE_BLOCK:
+        return block
+    out, run = [], 0
+    for line in block:
+        out.append(line)
+        if _VALU.match(line):
+            run += 1
+            if run == PACE:
+                out.append("\ts_nop 0")
+                run = 0
+        elif _OTHER.match(line):
+            run = 0
+    return out
+
+
+def pace(asm: str) -> tuple[str, int]:
+    """The assembly with the functions that hold MARK spaced; and how many."""
+    out, fn, n = [], [], 0
+
+    def close():
+        nonlocal n
+        if not any(MARK in l for l in fn):
+            out.extend(fn)
+            return
+        n += 1
+        block = []
+        for line in fn:
+            label = line[:1] not in ("", "\t", " ", ";", "#") and ":" in line
+            if label:
+                out.extend(_space(block))
+                block = []
+            block.append(line)
+            if _ENDS.match(line):
+                out.extend(_space(block))
+                block = []
+        out.extend(_space(block))
+
+    for line in asm.split("\n"):
+        fn.append(line)
+        if line.startswith(".Lfunc_end"):
+            close()
+            fn = []
+    out.extend(fn)
+    return "\n".join(out), n
+
+
+def _compile(src: str, obj: str, extra: list[str]) -> None:
+    path = os.path.join(HERE, src)
+    flags = [*FLAGS, *extra]
+
+    def run(*cmd):
+        subprocess.run(cmd, check=True)
+
+    with open(path) as f:
+        paced = "FIB_PACED" in f.read()
+    if not paced:
+        run(HIPCC, *flags, "-c", path, "-o", obj)
+        return
+    asm, dev, co, fatbin = (obj + e for e in (".s", ".dev.o", ".co", ".hipfb"))
+    run(HIPCC, *flags, "--offload-device-only", "-S", path, "-o", asm)
+    with open(asm) as f:
+        text, n = pace(f.read())
+    if not n:
+        raise RuntimeError(f"{src}: no paced kernel in the assembly")
+    with open(asm, "w") as f:
+        f.write(text)
+    run(os.path.join(LLVM, "clang"), "-x", "assembler", "-target", "amdgcn-amd-amdhsa",
+        f"-mcpu={ARCH}", "-c", asm, "-o", dev)
+    run(os.path.join(LLVM, "ld.lld"), "-shared", dev, "-o", co)
+    run(os.path.join(LLVM, "clang-offload-bundler"), "-type=o", "-bundle-align=4096",
+        f"-targets=host-x86_64-unknown-linux-gnu,hipv4-amdgcn-amd-amdhsa--{ARCH}",
+        "-input=/dev/null", f"-input={co}", f"-output={fatbin}")
+    run(HIPCC, *flags, "--offload-host-only", "-Xclang", "-fcuda-include-gpubinary",
+        "-Xclang", fatbin, "-c", path, "-o", obj)
+
 
 def build(verbose: bool = False, extra=None) -> str:
-    srcs = [os.path.join(HERE, s) for s in SOURCES]
+    extra = list(extra or [])
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, *(extra or []), "-o", tmp, *srcs]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, s + ".o") for s in SOURCES]
+        with concurrent.futures.ThreadPoolExecutor(4) as pool:
+            for s, job in [(s, pool.submit(_compile, s, o, extra))
+                           for s, o in zip(SOURCES, objs)]:
+                job.result()
+                if verbose:
+                    print(s, flush=True)
+        subprocess.run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs],
+                       check=True)
     os.replace(tmp, LIB)
     return LIB
 

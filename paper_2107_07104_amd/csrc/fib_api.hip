@@ -760,9 +760,10 @@ void window_rule(fib_ctx* c) {
 // windows, and their estimated cycles per split step.  A launch of S steps
 // computes halo = S width nodes beyond a block's own at either side, so more
 // steps share a launch's fixed cost but more nodes are computed twice.  The
-// costs are measured: about 1100 cycles per step for each wave a SIMD holds
-// (at least 1500, one wave's own chain), 300 for the exchange, and 9000 per
-// launch.
+// costs are measured (cycles): 850 per step for each wave a SIMD holds, 1300
+// for the step's chain and exchange, 6500 per launch and resident block (us
+// per step, rule / measured: 36 083 nodes at 512 threads and 16 steps 1.42 /
+// 1.27, 126 229 at 768 and 12 1.83 / 1.76, 419 886 at 1024 and 10 3.92 / 4.02).
 double window_plan(int64_t nodes, int width, int cus, fib::WindowPlan& p) {
   double best = INFINITY;
   for (int threads = 256; threads <= 1024; threads += 128) {
@@ -771,7 +772,7 @@ double window_plan(int64_t nodes, int width, int cus, fib::WindowPlan& p) {
       if (own < 16) break;
       const int64_t blocks = (nodes + own - 1) / own;
       const double per_cu = (double)((blocks + cus - 1) / cus);
-      const double cost = 1100.0 + 1000.0 * per_cu * ((threads + 255) / 256) + 6500.0 * per_cu / S;
+      const double cost = 1300.0 + 850.0 * per_cu * ((threads + 255) / 256) + 6500.0 * per_cu / S;
       if (cost < best) {
         best = cost;
         p = fib::WindowPlan{threads, S};
@@ -810,9 +811,10 @@ void window_setup(fib_ctx* c, bool steps) {
 // diffusion, or whole Hodgkin-Huxley steps on windows; schedule AUTO takes
 // the latter in place of the fused kernel where that leaves much of the chip
 // idle.  The fused kernel's cost by the same measure: 2100 cycles per step and
-// 980 for each node of a SIMD's threads (us per step, fused / windows: 1000
-// nodes 2.55 / 1.07, 36 083 2.56 / 1.43, 126 229 2.75 / 1.92, 419 886 5.40 / 4.43;
-// the 1369-fiber bundle 12.4 / 19.4).
+// for each node of a SIMD's threads 820, or 980 where one wave is alone on it
+// (us per step, fused / windows: 1000 nodes 2.25 / 1.06, 36 083 2.20 / 1.27,
+// 126 229 2.29 / 1.76, 419 886 4.69 / 4.02; the 1369-fiber bundle 10.5 / 15.7
+// by the rule).
 void window_create(fib_ctx* c) {
   window_rule(c);
   if (c->win.width == 0) return;
@@ -825,7 +827,8 @@ void window_create(fib_ctx* c) {
   if (c->p.schedule == FIB_SCHED_AUTO) {
     const bool automatic = c->p.threads_per_group == 0 && c->p.nodes_per_thread == 0 &&
                            c->p.groups == 0 && c->p.tune == 0;
-    c->win_auto = automatic && cost < (c->threads + 255) / 256 * c->K * 980.0 + 2100.0;
+    const int waves = (c->threads + 255) / 256;
+    c->win_auto = automatic && cost < waves * c->K * (waves > 1 ? 820.0 : 980.0) + 2100.0;
   }
   if (c->win_auto || c->p.schedule == FIB_SCHED_SPLIT) window_setup(c, true);
 }

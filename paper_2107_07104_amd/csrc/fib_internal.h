@@ -8,6 +8,19 @@
 
 namespace fib {
 
+// Marks a kernel whose vector instructions the build spaces with s_nop
+// (build.py): one that mixes transcendentals into them and runs two waves or
+// more per SIMD.  Where both happen a kernel has a paced and a plain instance
+// and two_waves() chooses, since a wave alone on its SIMD is 12 % slower with
+// the s_nop and two together are 20 % faster.
+#define FIB_PACED(on)                                \
+  do {                                               \
+    if constexpr (on) asm volatile("; fib paced");   \
+  } while (0)
+// Whether some SIMD gets a second wave of a launch: a workgroup of more than
+// four waves, or more workgroups than compute units.
+bool two_waves(int64_t groups, int threads);
+
 // Stimulus entry as the kernels see it: step indices as int32.
 struct StimDev {
   int32_t on;      // first split step the entry is on in

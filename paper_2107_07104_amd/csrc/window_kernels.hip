@@ -168,16 +168,18 @@ __global__ __launch_bounds__(256) void k_diffuse_window(KArgs A, WindowStencil s
 // V_m prescriptions, R(dt/2) D(dt) R(dt/2) (Godunov: R(dt) D(dt)), the
 // observables; the states stay in registers throughout.
 //
-// Bound by vector issue like k_run_hh (0.35-0.45 us per step for each wave a
-// SIMD holds) and by one step's own chain (0.5 us: four right-hand sides and
-// one barrier, where the fused kernel has 3 + L), and by the launch (2.7 us)
-// shared by wa.steps steps.  Where fibers are few or short this fills the chip
-// as whole-fiber workgroups cannot: one fiber of 1000 nodes 2.5 -> 1.07 us per
-// step, 200 fibers of 301-977 nodes 2.7 -> 1.9 us against the fused kernel and
-// 10.5 -> 2.1 us against one reaction and one diffusion launch per step.
-template <bool APX, int W>
+// Bound by vector issue like k_run_hh (0.35 us per step for each wave a SIMD
+// holds; paced as that is, 0.42 without) and by one step's own chain (0.5 us:
+// four right-hand sides and one barrier, where the fused kernel has 3 + L),
+// and by the launch (2.7 us) shared by wa.steps steps.  Where fibers are few
+// or short this fills the chip as whole-fiber workgroups cannot: one fiber of
+// 1000 nodes 2.25 -> 1.06 us per step, 200 fibers of 301-977 nodes 2.3 -> 1.8
+// us against the fused kernel and 10.5 -> 1.9 us against one reaction and one
+// diffusion launch per step.
+template <bool APX, int W, bool PACED>
 __global__ __launch_bounds__(1024) void k_window_hh(KArgs A, WindowStencil st, WindowArgs wa,
                                                     int32_t step0) {
+  FIB_PACED(PACED);
   extern __shared__ float s_v[];  // two buffers of blockDim.x + 2 kPad
   const int T = blockDim.x, t = threadIdx.x, row = T + 2 * kPad<W>;
   const int64_t nt = A.n_total;
@@ -277,12 +279,13 @@ __host__ __device__ inline size_t adapt_fiber_lds(int n) {
 // Bound by the reaction's chain (six right-hand sides per half, 6-7 us) on the
 // few waves the solved nodes fill; the four launches it replaces took 65 us
 // per step on 400 x 1481 nodes with 6 % firing (22 of them reading flags), this
-// 33.  Fibers are independent, so no other synchronization is needed;
-// with more fibers than compute units workgroups of four waves run two to a
-// unit, else of eight.
+// 30 (34 before it was paced).  Fibers are independent, so no other
+// synchronization is needed; with more fibers than compute units workgroups
+// of four waves run two to a unit, else of eight.
 template <bool GODUNOV, int W>
 __global__ __launch_bounds__(512, 2) void k_run_st57_adapt(KArgs A, WindowStencil st,
                                                            const int32_t* __restrict__ first) {
+  FIB_PACED(true);
   constexpr int S = st57::S;
   extern __shared__ __align__(16) char smem[];
   const int f = blockIdx.x, t = threadIdx.x, T = blockDim.x, lane = t & 63;
@@ -558,13 +561,19 @@ hipError_t launch_window_hh(bool apx, const WindowStencil& st, const WindowArgs&
   if (a.n_total == 0) return hipSuccess;
   const dim3 grid((unsigned)((a.n_total + wa.own - 1) / wa.own)), block((unsigned)p.threads);
   const size_t lds = 2 * sizeof(float) * (size_t)(p.threads + 2 * st.width);
-#define FIB_LAUNCH(W)                                                                       \
-  if (st.width == W) {                                                                      \
-    if (apx) hipLaunchKernelGGL((k_window_hh<true, W>), grid, block, lds, s, a, st, wa, step0); \
-    else hipLaunchKernelGGL((k_window_hh<false, W>), grid, block, lds, s, a, st, wa, step0);    \
+  const bool paced = two_waves(grid.x, p.threads);
+#define FIB_LAUNCH_(APX, W, PACED) \
+  hipLaunchKernelGGL((k_window_hh<APX, W, PACED>), grid, block, lds, s, a, st, wa, step0)
+#define FIB_LAUNCH(W)                                       \
+  if (st.width == W) {                                      \
+    if (apx && paced) FIB_LAUNCH_(true, W, true);           \
+    else if (apx) FIB_LAUNCH_(true, W, false);              \
+    else if (paced) FIB_LAUNCH_(false, W, true);            \
+    else FIB_LAUNCH_(false, W, false);                      \
   }
   FIB_FOR_EACH_WIDTH(FIB_LAUNCH)
 #undef FIB_LAUNCH
+#undef FIB_LAUNCH_
   return hipGetLastError();
 }
 
