@@ -339,9 +339,9 @@ __device__ __forceinline__ void heun(float (&u)[S], const float* __restrict__ re
   const float ht = 0.5f * tau;
 #pragma unroll
   for (int q = 0; q < S; ++q) {
-    const float w = fmaf(ht, k[q], u[q]);  // u + tau/2 k1
-    k[q] = fmaf(tau, k[q], u[q]);          // stage point u + tau k1
-    u[q] = w;
+    const float k1 = k[q];
+    k[q] = fmaf(tau, k1, u[q]);  // stage point u + tau k1
+    u[q] = fmaf(ht, k1, u[q]);   // u + tau/2 k1
   }
   float k2[S];
   rhs<float, APX>(k, ref, I, inv_cm, k2);
