@@ -1077,48 +1077,85 @@ __global__ __launch_bounds__(256) void k_react(KArgs A, int32_t step_a, int32_t 
 }
 
 // The same phases over a grid that fits on the device at once: a thread
-// takes nodes i, i + stride, ... and loads the next node's states before it
+// takes nodes i, i + stride, ... and loads the next node's states while it
 // solves the current one.  A model whose right-hand side holds few waves
-// per SIMD (ST57: two, at 242 VGPRs) has little else there to cover the
-// loads; this way they run under the wave's own arithmetic.  Loads return in issue order,
-// so everything the current node reads (stimulus entry, v_prev, t_act) is
-// read before the next node's loads are issued: waiting for it then does
-// not wait for them.
+// per SIMD (ST57: two) has little else there to cover the loads; this way
+// they run under the wave's own arithmetic.
 //
-// Bound by vector issue where the states are read at the rate the arithmetic
-// takes them: paced (two waves per SIMD), 400 x 1481 nodes 5.35 -> 4.45 ms
-// per 40 steps, 4e6 nodes 12.0 -> 10.2 ms per 16 steps.
+// Bound by vector issue (paced with two waves per SIMD: 400 x 1481 nodes 124
+// -> 105 us per launch) where nothing waits for memory.  A wave has at most
+// 63 accesses outstanding, loads and stores together, and a node has 57 of
+// each: so the next node's loads are issued half way through the current
+// one's substeps, when the previous node's stores have drained, and arrive in
+// the other half; and nothing between a node's stores and those loads waits
+// for the memory (a stimulus entry is read by the few waves that have one).
+// With the loads before the first substep, behind a wait for those stores,
+// and a vector address per row: 98.6 -> 105 us.
 template <class M, bool PACED>
-__global__ __launch_bounds__(256) void k_react_stream(KArgs A, int32_t step_a, int32_t step_b,
+__global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a, int32_t step_b,
                                                       int flags) {
   FIB_PACED(PACED);
   const int64_t nt = A.n_total;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const bool obs = flags & REACT_OBSERVE;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nt) return;
+  // the wave's first node, the same for all lanes (row addresses then take
+  // scalar additions, not 64-bit vector ones: 2 % of the instructions)
+  const int lane = threadIdx.x & 63;
+  int64_t i0 = (int64_t)blockIdx.x * blockDim.x +
+               __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+  if (i0 + lane >= nt) return;
   const int32_t base = step_base_of(A);
   step_a += base;
   step_b += base;
+  const int n_a = flags & REACT_A ? A.n_sub : 0;
+  const int n_all = n_a + (flags & REACT_B ? A.n_sub : 0);
+  // substeps before the next node's loads: the first phase of two, half of one
+  const bool both = n_a > 0 && n_all > n_a;
+  const int half = both ? n_a : n_all / 2;
   // the next node's inputs: states, stimulus entry, v_prev and t_act
   float nx[M::S];
-  uint32_t nsid = (uint32_t)A.node_stim[i];
-  float nv0 = obs ? A.v_prev[i] : 0.0f, nta = obs ? A.t_act[i] : 0.0f;
+  auto load = [&](int64_t first) {
+    gfloat* row = (gfloat*)(A.state + first);
 #pragma unroll
-  for (int k = 0; k < M::S; ++k) nx[k] = A.state[k * nt + i];
-  for (; i < nt; i += stride) {
+    for (int k = 0; k < M::S; ++k, row += nt) {
+      asm("" : "+s"(row));
+      nx[k] = row[lane];
+    }
+  };
+  uint32_t nsid = (uint32_t)A.node_stim[i0 + lane];
+  float nv0 = obs ? A.v_prev[i0 + lane] : 0.0f, nta = obs ? A.t_act[i0 + lane] : 0.0f;
+  load(i0);
+  // waited for before the loop, whose own wait then counts a node's stores
+  // as issued after its loads
+#pragma unroll
+  for (int k = 0; k < M::S; ++k) asm volatile("" : "+v"(nx[k]));
+  for (; i0 + lane < nt; i0 += stride) {
+    const int64_t i = i0 + lane;
     float u[M::S];
 #pragma unroll
     for (int k = 0; k < M::S; ++k) u[k] = nx[k];
-    const uint32_t sid = nsid;
-    float v0 = nv0, ta = nta;
+    const float v0 = nv0, ta = nta;
     float Ia = 0.0f, Ib = 0.0f, vb = 0.0f;
     int set_b = 0;
-    if (flags & REACT_A) Ia = stim_current(sid, A.stim, step_a);
-    if (flags & REACT_B) set_b = stim_eval(sid, A.stim, step_b, Ib, vb);
-    // all of them in registers here, so no later wait for one of them waits
-    // for the next node's loads too
-    asm volatile("" : "+v"(Ia), "+v"(Ib), "+v"(vb), "+v"(set_b), "+v"(v0), "+v"(ta));
+    if (nsid) {
+      StimDev e = A.stim[nsid - 1];
+      // all of it waited for here, by these lanes' waves only
+      asm volatile("" : "+v"(e.on), "+v"(e.dur), "+v"(e.period), "+v"(e.amp),
+                   "+v"(e.voltage));
+      if (!e.voltage && stim_on(e, step_a)) Ia = e.amp;
+      if ((flags & REACT_B) && stim_on(e, step_b)) {
+        set_b = e.voltage;
+        (e.voltage ? vb : Ib) = e.amp;
+      }
+    }
+    float I = Ia;
+    auto between = [&] {  // the end of step_a and the start of step_b
+      if (obs) observe_step_from(A, i, step_a, v0, ta, u[0]);
+      if (set_b) u[0] = vb;
+      I = Ib;
+    };
+    if (n_a == 0) between();
+    for (int s = 0; s < half; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
     const int64_t j = i + stride;
     if (j < nt) {
       nsid = (uint32_t)A.node_stim[j];
@@ -1126,19 +1163,18 @@ __global__ __launch_bounds__(256) void k_react_stream(KArgs A, int32_t step_a, i
         nv0 = A.v_prev[j];
         nta = A.t_act[j];
       }
-#pragma unroll
-      for (int k = 0; k < M::S; ++k) nx[k] = A.state[k * nt + j];
+      load(i0 + stride);
     }
-    if (flags & REACT_A)
-      for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, Ia, A.tau, A.inv_cm);
-    if (obs) observe_step_from(A, i, step_a, v0, ta, u[0]);
-    if (flags & REACT_B) {
-      if (set_b) u[0] = vb;
-      for (int s = 0; s < A.n_sub; ++s) M::heun(u, A.rest, Ib, A.tau, A.inv_cm);
-    }
+    if (both) between();
+    for (int s = half; s < n_all; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
+    if (n_a == n_all) between();
     A.v_out[i] = u[0];
+    gfloat* row = (gfloat*)(A.state + (nt + i0));
 #pragma unroll
-    for (int k = 1; k < M::S; ++k) A.state[k * nt + i] = u[k];
+    for (int k = 1; k < M::S; ++k, row += nt) {
+      asm("" : "+s"(row));
+      row[lane] = u[k];
+    }
   }
 }
 
