@@ -48,6 +48,31 @@ constexpr int MAX_STATES = 64;
 // count against the LDS wait counter.
 typedef __attribute__((address_space(1))) float gfloat;
 
+// Whether a pass over S state rows of n_total nodes streams them past the
+// caches (non-temporal loads and stores). Each is read and written once a
+// pass, so past what the last-level cache (256 MB) can hold of them from pass
+// to pass they only displace the rows that are read again (V_m, the stimulus
+// entries). us per 8 steps of the 57-state model, cached / streamed, plain |
+// Euler predictor | network: 134 MB 911 / 1011 | 700 / 852 | 1032 / 1086, 302
+// MB 1961 / 1976 | 1488 / 1544 | 1919 / 1902, 402 MB 2563 / 2565 | 2005 / 1972
+// | 2418 / 2361, 839 MB 4942 / 4834 | 3899 / 3732 | 4473 / 4212. Rows that do
+// not start on a 128-byte line lose instead (844 MB: 6487 for 5276 plain):
+// two waves share each line at their ends, and without the caches it is moved
+// for both.
+inline bool stream_states(int64_t n_total, int S) {
+  return n_total % 32 == 0 && n_total * S * 4 > (int64_t)384 << 20;
+}
+template <bool STREAM>
+__device__ __forceinline__ float read_state(gfloat* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  return *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void write_state(gfloat* p, float v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // Point flags of the adaptive computation, one byte per node and step:
 //   PT_SOLVE:  the node is solved in this step (set by the start kernel,
 //              consumed by the finish kernel of a Strang step);

@@ -1091,7 +1091,7 @@ __global__ __launch_bounds__(256) void k_react(KArgs A, int32_t step_a, int32_t 
 // for the memory (a stimulus entry is read by the few waves that have one).
 // With the loads before the first substep, behind a wait for those stores,
 // and a vector address per row: 98.6 -> 105 us.
-template <class M, bool PACED>
+template <class M, bool PACED, bool STREAM>
 __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a, int32_t step_b,
                                                       int flags) {
   FIB_PACED(PACED);
@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
 #pragma unroll
     for (int k = 0; k < M::S; ++k, row += nt) {
       asm("" : "+s"(row));
-      nx[k] = row[lane];
+      nx[k] = read_state<STREAM>(row + lane);
     }
   };
   uint32_t nsid = (uint32_t)A.node_stim[i0 + lane];
@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
 #pragma unroll
     for (int k = 1; k < M::S; ++k, row += nt) {
       asm("" : "+s"(row));
-      row[lane] = u[k];
+      write_state<STREAM>(row + lane, u[k]);
     }
   }
 }
@@ -1583,7 +1583,7 @@ static unsigned st57_stream_blocks() {
   if (cache[dev] == 0) {
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_react_stream<M, true>, 256,
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_react_stream<M, true, false>, 256,
                                                       0) != hipSuccess ||
         cus <= 0 || per_cu <= 0)
       return ~0u;
@@ -1596,12 +1596,13 @@ template <class M>
 static void react_stream(unsigned blocks, int32_t step_a, int32_t step_b, int flags,
                          const KArgs& a, hipStream_t s) {
   const unsigned grid = std::min(blocks, st57_stream_blocks<M>());
-  if (two_waves(grid, 256))
-    hipLaunchKernelGGL((k_react_stream<M, true>), dim3(grid), dim3(256), 0, s, a, step_a, step_b,
-                       flags);
-  else
-    hipLaunchKernelGGL((k_react_stream<M, false>), dim3(grid), dim3(256), 0, s, a, step_a, step_b,
-                       flags);
+#define FIB_LAUNCH(PACED, STREAM)                                                               \
+  hipLaunchKernelGGL((k_react_stream<M, PACED, STREAM>), dim3(grid), dim3(256), 0, s, a, step_a, \
+                     step_b, flags)
+  if (stream_states(a.n_total, M::S)) FIB_LAUNCH(true, true);
+  else if (two_waves(grid, 256)) FIB_LAUNCH(true, false);
+  else FIB_LAUNCH(false, false);
+#undef FIB_LAUNCH
 }
 
 hipError_t launch_react(int model, int32_t step_a, int32_t step_b, int flags, const KArgs& a,

@@ -316,7 +316,7 @@ __device__ __forceinline__ void wave_network(char* stage, const v8bf* __restrict
 // Persistent: each wave walks the 64-node tiles tile = wave_id,
 // wave_id + waves, ...  Launch: 64 WAVES threads.
 template <class M, int KIN_PAD, int H, int NHID, int OUT_PAD, int ACT, int WAVES, int NG,
-          int NCORR>
+          int NCORR, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES) void k_surrogate(
     KArgs A, SurrogateNet net, const __bf16* __restrict__ frags, const float* __restrict__ biases,
     const float* __restrict__ tab_g, SurrogateScales sc, int32_t step_a, int* __restrict__ list,
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_surrogate(
       Column col{A.state + ic, nt};
 #pragma unroll
       for (int k = 0; k < S; ++k) {
-        u[k] = *col.p;
+        u[k] = read_state<STREAM>(col.p);
         col.next();
       }
     }
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_surrogate(
         Column col{A.state + nt + i, nt};
 #pragma unroll
         for (int k = 1; k < S; ++k) {
-          col.p[0] = fmaf(span, G[k], u[k]);
+          write_state<STREAM>(col.p, fmaf(span, G[k], u[k]));
           col.next();
         }
       }
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_surrogate(
 // current one.  Every lane of a wave runs the same rounds (lanes past the
 // end read the last node and drop their results), so the ballot below sees
 // whole waves.  Launch: 256 threads.
-template <class M, int PRED, int NCORR>
+template <class M, int PRED, int NCORR, bool STREAM>
 __global__ __launch_bounds__(256, 2) void k_midpoint(KArgs A, const float* __restrict__ tab_g,
                                                   int32_t step_a, int* __restrict__ list,
                                                   int* __restrict__ counts, int slot) {
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(256, 2) void k_midpoint(KArgs A, const float* __res
       nv0 = A.v_prev[jc];
       nta = A.t_act[jc];
 #pragma unroll
-      for (int k = 0; k < S; ++k) nx[k] = A.state[k * nt + jc];
+      for (int k = 0; k < S; ++k) nx[k] = read_state<STREAM>((gfloat*)(A.state + (k * nt + jc)));
     }
     float y[S], G[S], du[S];
     if constexpr (PRED == FIB_PRED_EULER) {
@@ -602,7 +602,8 @@ __global__ __launch_bounds__(256, 2) void k_midpoint(KArgs A, const float* __res
       if (!isfinite(v1)) atomicOr(A.flag, 1);
       A.v_out[i] = fmaf(span, G[0], u[0]);
 #pragma unroll
-      for (int k = 1; k < S; ++k) A.state[k * nt + i] = fmaf(span, G[k], u[k]);
+      for (int k = 1; k < S; ++k)
+        write_state<STREAM>((gfloat*)(A.state + (k * nt + i)), fmaf(span, G[k], u[k]));
     }
     const bool reject = real && !ok;
     const uint64_t mask = __ballot(reject);
@@ -706,10 +707,14 @@ static hipError_t sur_launch(const KArgs& a, const SurrogateNet& net, const __bf
   const int64_t tiles = (a.n_total + 63) / 64;
   const int64_t need = (tiles + C::WAVES - 1) / C::WAVES;
   const unsigned blocks = (unsigned)(need < grid ? need : grid);
-  hipLaunchKernelGGL((k_surrogate<M, C::KIN_PAD, C::H, C::NHID, C::OUT_PAD, ACT, C::WAVES, C::NG,
-                                  C::NCORR>),
-                     dim3(blocks), dim3(64 * C::WAVES), lds, s, a, net, frags, biases, tab, sc,
-                     step_a, list, counts, slot, pred);
+#define FIB_LAUNCH(STREAM)                                                                     \
+  hipLaunchKernelGGL((k_surrogate<M, C::KIN_PAD, C::H, C::NHID, C::OUT_PAD, ACT, C::WAVES,     \
+                                  C::NG, C::NCORR, STREAM>),                                   \
+                     dim3(blocks), dim3(64 * C::WAVES), lds, s, a, net, frags, biases, tab, sc, \
+                     step_a, list, counts, slot, pred)
+  if (stream_states(a.n_total, M::S)) FIB_LAUNCH(true);
+  else FIB_LAUNCH(false);
+#undef FIB_LAUNCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || pred) return e;
   if (mid && (e = hipEventRecord(mid, s)) != hipSuccess) return e;
@@ -747,7 +752,7 @@ static unsigned midpoint_resident_blocks() {
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, k_midpoint<M, PRED, SurCfg<M>::NCORR>, 256, 0) != hipSuccess ||
+            &per_cu, k_midpoint<M, PRED, SurCfg<M>::NCORR, false>, 256, 0) != hipSuccess ||
         cus <= 0 || per_cu <= 0)
       return 0;
     cache[dev] = (unsigned)cus * (unsigned)per_cu;
@@ -763,8 +768,12 @@ static hipError_t pred_launch(const KArgs& a, const float* tab, int32_t step_a, 
   const unsigned resident = midpoint_resident_blocks<M, PRED>();
   const int64_t cap = resident > 0 ? (int64_t)resident : need;
   const unsigned blocks = (unsigned)(need < cap ? need : cap);
-  hipLaunchKernelGGL((k_midpoint<M, PRED, SurCfg<M>::NCORR>), dim3(blocks), dim3(256), 0, s, a,
-                     tab, step_a, list, counts, slot);
+  if (stream_states(a.n_total, M::S))
+    hipLaunchKernelGGL((k_midpoint<M, PRED, SurCfg<M>::NCORR, true>), dim3(blocks), dim3(256), 0,
+                       s, a, tab, step_a, list, counts, slot);
+  else
+    hipLaunchKernelGGL((k_midpoint<M, PRED, SurCfg<M>::NCORR, false>), dim3(blocks), dim3(256), 0,
+                       s, a, tab, step_a, list, counts, slot);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (mid && (e = hipEventRecord(mid, s)) != hipSuccess) return e;

@@ -14,6 +14,7 @@ from paper_2107_07104_amd import fib as F
 from paper_2107_07104_amd import inputs as I
 
 from gpu_helpers import gpu_solver, say
+from test_gpu_surrogate import _random_net
 
 torch = pytest.importorskip("torch")
 
@@ -65,3 +66,38 @@ def test_copies_of_a_fiber_are_bitwise_equal(n_fibers, n, dt_0D, splitting):
         c = len(range(f, n_fibers, 3))
         np.testing.assert_array_equal(y[:, f::3], np.broadcast_to(y0[:, f:f + 1], (S, c, n)))
         np.testing.assert_array_equal(t[f::3], np.broadcast_to(t0[f:f + 1], (c, n)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("path", ["plain", "euler", "zero", "network"])
+@pytest.mark.parametrize("n_fibers,n", [(13800, 128), (13799, 128), (14001, 127)])
+def test_streamed_states_are_the_cached_ones(n_fibers, n, path):
+    """Bundles past the last-level cache whose rows start on a line (13 800 and
+    13 799 fibers of 128 nodes: 403 MB, just past the rule) or not."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    steps = 5
+    say(f"[streamed states] {n_fibers} x {n} {path}")
+    sizes, _, net = _random_net(I.MODEL_ST57, 3)
+    out = []
+    for fibers in (n_fibers, 3):
+        w = _bundle(fibers, n, steps)
+        s = gpu_solver(w)
+        if path == "network":
+            s.set_surrogate(net, dict(in_shift=np.zeros(57), in_scale=np.ones(57),
+                                      out_shift=np.zeros(57), out_scale=np.full(57, 1e-6),
+                                      res_scale=np.ones(57), flag_scale=1.0), 1e30)
+        elif path != "plain":
+            s.set_predictor(F.FIB_PRED_EULER if path == "euler" else F.FIB_PRED_ZERO,
+                            np.ones(57, dtype=np.float32), 1e30)
+        s.run(0, steps)
+        s.sync()
+        y = s.get_state()
+        assert np.isfinite(y).all()
+        out.append(y.reshape(57, fibers, n))
+        s.close()
+    net.close()
+    for f in range(3):
+        c = len(range(f, n_fibers, 3))
+        np.testing.assert_array_equal(out[0][:, f::3],
+                                      np.broadcast_to(out[1][:, f:f + 1], (57, c, n)))
