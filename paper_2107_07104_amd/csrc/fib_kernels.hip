@@ -1088,9 +1088,10 @@ __global__ __launch_bounds__(256) void k_react(KArgs A, int32_t step_a, int32_t 
 // each: so the next node's loads are issued half way through the current
 // one's substeps, when the previous node's stores have drained, and arrive in
 // the other half; and nothing between a node's stores and those loads waits
-// for the memory (a stimulus entry is read by the few waves that have one).
-// With the loads before the first substep, behind a wait for those stores,
-// and a vector address per row: 98.6 -> 105 us.
+// for the memory: the next node's stimulus entry is read, by the few waves
+// that have one, before the stores (the first node's while its states are on
+// their way).  With the loads before the first substep, behind a wait for
+// those stores, and a vector address per row: 98 -> 105 us.
 template <class M, bool PACED, bool STREAM>
 __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a, int32_t step_b,
                                                       int flags) {
@@ -1125,18 +1126,12 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
   uint32_t nsid = (uint32_t)A.node_stim[i0 + lane];
   float nv0 = obs ? A.v_prev[i0 + lane] : 0.0f, nta = obs ? A.t_act[i0 + lane] : 0.0f;
   load(i0);
-  // waited for before the loop, whose own wait then counts a node's stores
-  // as issued after its loads
-#pragma unroll
-  for (int k = 0; k < M::S; ++k) asm volatile("" : "+v"(nx[k]));
-  for (; i0 + lane < nt; i0 += stride) {
-    const int64_t i = i0 + lane;
-    float u[M::S];
-#pragma unroll
-    for (int k = 0; k < M::S; ++k) u[k] = nx[k];
-    const float v0 = nv0, ta = nta;
-    float Ia = 0.0f, Ib = 0.0f, vb = 0.0f;
-    int set_b = 0;
+  // the next node's stimulus
+  float Ia, Ib, vb;
+  int set_b;
+  auto stimulus = [&] {
+    Ia = Ib = vb = 0.0f;
+    set_b = 0;
     if (nsid) {
       StimDev e = A.stim[nsid - 1];
       // all of it waited for here, by these lanes' waves only
@@ -1148,6 +1143,18 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
         (e.voltage ? vb : Ib) = e.amp;
       }
     }
+  };
+  stimulus();
+  // waited for before the loop, whose own wait then counts a node's stores
+  // as issued after its loads
+#pragma unroll
+  for (int k = 0; k < M::S; ++k) asm volatile("" : "+v"(nx[k]));
+  for (; i0 + lane < nt; i0 += stride) {
+    const int64_t i = i0 + lane;
+    float u[M::S];
+#pragma unroll
+    for (int k = 0; k < M::S; ++k) u[k] = nx[k];
+    const float v0 = nv0, ta = nta;
     float I = Ia;
     auto between = [&] {  // the end of step_a and the start of step_b
       if (obs) observe_step_from(A, i, step_a, v0, ta, u[0]);
@@ -1168,6 +1175,7 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
     if (both) between();
     for (int s = half; s < n_all; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
     if (n_a == n_all) between();
+    if (j < nt) stimulus();
     A.v_out[i] = u[0];
     gfloat* row = (gfloat*)(A.state + (nt + i0));
 #pragma unroll
