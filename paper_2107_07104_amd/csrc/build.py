@@ -41,7 +41,7 @@ SOURCES = ["fib_api.hip", "fib_kernels.hip", "mlp_api.hip", "mlp_kernels.hip",
            "surrogate_kernels.hip", "window_kernels.hip",
            "emg.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-LLVM = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "llvm", "bin")
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
 ARCH = "gfx950"
 PACE = 6          # vector instructions between two s_nop
 PACE_BLOCK = 48   # of a basic block that is spaced, at least
