@@ -94,7 +94,8 @@ struct KArgs {
   const int32_t* node_stim; // [n_total], stimulus entry + 1 (0: none)
   const StimDev* stim;      // stimulus table
   float* t_act;             // [n_total]
-  float* v_prev;            // [n_total], V_m at the end of the previous split step (SPLIT)
+  float* v_prev;            // [n_total], V_m at the end of the previous split step: every
+                            // run leaves it, a surrogate step reads it
   float* samples;           // [rows][n_total] or null
   int64_t sample_every;     // 0: no samples
   int64_t sample_row0;      // rows written by earlier calls: step0 / sample_every

@@ -473,6 +473,7 @@ __global__ __launch_bounds__(512, 2) void k_run_st57_adapt(KArgs A, WindowStenci
   for (int i = t; i < N; i += T) {
     const float v = v_in[i];
     A.state[off + i] = v;
+    A.v_prev[off + i] = v;  // a surrogate step may follow
     A.pt_cur[off + i] = act[par][i] ? PT_ACTIVE : 0;
     bad |= !isfinite(v);
   }
