@@ -293,7 +293,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
           if (GRAD)
             *reinterpret_cast<v4f*>(lds + t.z[l] + 16 * ((sb * ob_n + ob) * 64 + lane)) = v;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = act_fn(s.act, v[j]);
+          for (int j = 0; j < 4; ++j)  // padding stays 0 where an activation is not finite
+            v[j] = f + j < nout ? act_fn(s.act, v[j]) : 0.0f;
           store_operand(v, dst, t.xstride,
                         GRAD ? reinterpret_cast<__bf16*>(lds + t.xt[l]) : nullptr, n, f);
         } else {
