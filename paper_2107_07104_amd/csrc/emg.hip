@@ -921,9 +921,12 @@ int fdm_solve(fib_emg* e, const fib::CtxView& v, double tol, int32_t max_iter) {
                      tol * tol, e->d_s);
   // Two iterations reach 1e-8 and more on the meshes measured (2 x 2 x 3 to 37
   // x 37 x 149, 3 x 2 x 1481), so that many are enqueued before the host
-  // looks, then one at a time; launches past convergence return at once.
+  // looks, then one at a time, and half as many as were taken once it is clear
+  // that more are needed (a look costs about an iteration: 2000 one by one
+  // took 110 ms); launches past convergence return at once.
   int32_t launched = 0;
-  for (int batch = 2;; batch = 1) {
+  for (;;) {
+    const int batch = launched == 0 ? 2 : std::min(std::max(launched / 2 - 1, 1), 32);
     const int n_it = std::min(batch, max_iter - launched);
     for (int b = 0; b < n_it; ++b) {
       const int P = (launched + b) & 1;
@@ -946,6 +949,12 @@ int fdm_solve(fib_emg* e, const fib::CtxView& v, double tol, int32_t max_iter) {
     EHIP(hipMemcpyAsync(e->h_s, e->d_s, sizeof(Scal), hipMemcpyDeviceToHost, st));
     EHIP(hipStreamSynchronize(st));
     if (e->h_s->done || last) return FIB_OK;
+    if (std::isnan(e->h_s->bb)) {
+      // V_m is not finite: phi_e is NaN, and every further iteration leaves it
+      // so
+      e->h_s->it = max_iter;
+      return FIB_OK;
+    }
   }
 }
 
