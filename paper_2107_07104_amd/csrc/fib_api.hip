@@ -782,6 +782,43 @@ double window_plan(int64_t nodes, int width, int cus, fib::WindowPlan& p) {
   return best;
 }
 
+// Whether the diffusion launches of the split schedule take the stencil or the
+// partitioned solve in place, by their cost in us.  The partitioned solve costs
+// more with the nodes per thread, the levels, the threads and the fibers of a
+// bin, and with the slots (more where large workgroups leave fewer of them
+// resident); the stencil with its width: the latency of the nodes near an end,
+// which read one neighbour after the other from LDS, and by the node, more
+// where a wave's 256 nodes often hold an end.  A least-squares fit to both
+// solves' times in runs of the Hodgkin-Huxley Euler predictor (24 bundles of
+// 1 to 8000 fibers of 50 to 8000 nodes, widths 8 to 32, plans of both
+// schedules: 288 pairs); where it picks the slower one, that is behind by 6 %
+// of the step at most.  us per step, partitioned / stencil, at widths 10, 16,
+// 24, 32:
+//   400 x 101, 20 fibers a bin       16.1 / 11.4  20.4 / 16.4  26.3 / 23.1  26.4 / 24.3
+//   1369 x 1000-1500, 5 a bin        34.2 / 30.1  40.5 / 38.0  82.7 / 82.8  97.0 / 100.9
+//   4000 x 1000, 2 a bin             64.4 / 52.0  76.4 / 67.4   198 / 195    239 / 242
+//   1000 x 4000, a bin each of 1024  56.5 / 49.8  59.0 / 54.5  84.8 / 82.5  99.2 / 100.7
+//   1369 x 1481, a bin each          34.5 / 34.0  39.3 / 40.9  82.7 / 87.5  96.9 / 103.8
+//   200 x 600, a bin each            11.7 / 11.9  14.6 / 15.3  21.8 / 23.4  23.4 / 26.1
+// With adaptive computation of the Hodgkin-Huxley model a bin without a solved
+// fiber is skipped, and V_m of every node is written for the stencil, so bins
+// of one fiber take the partitioned solve (width 10, 6 / 25 / 80 % firing, 1369
+// x 1000-1500: 30.0 32.6 43.0 / 33.1 35.2 43.6; 4000 x 1000, 2 a bin: 64.5
+// 70.3 90.2 / 59.4 63.7 81.9).
+bool diffuse_windowed(const fib_ctx* c, bool adaptive) {
+  if (c->win.width == 0 || !c->d_vmid) return false;
+  const double per_bin = (double)c->n_fibers / c->groups;
+  if (adaptive && c->p.model == FIB_MODEL_HH && per_bin < 1.5) return false;
+  const double w = c->win.width / 16.0, nodes = 1e-6 * (double)c->n_total,
+               slots = 1e-6 * (double)c->groups * c->cap, T = c->threads / 1024.0;
+  const double near_end =
+      std::min(1.0, (256.0 + 2.0 * c->win.width) * c->n_fibers / (double)c->n_total);
+  const double partitioned = 0.47 * c->K + 0.40 * c->levels + 0.75 * T +
+                             0.92 * std::log2(std::max(per_bin, 1.0)) + slots * (0.79 + 1.32 * T);
+  const double stencil = 1.30 + w * (2.14 + nodes * (0.93 + 2.72 * near_end));
+  return stencil < partitioned;
+}
+
 // Device data of the windowed diffusion (once; without memory for it the
 // partitioned solve stays).
 void window_setup(fib_ctx* c, bool steps) {
@@ -1038,7 +1075,7 @@ int run_adaptive(fib_ctx* c, KArgs a, int64_t step0, int64_t n_steps) {
   HIP_TRY(hipMemcpyAsync(c->d_vprev, c->d_state, sizeof(float) * nt, hipMemcpyDeviceToDevice,
                          c->stream));
   const size_t lds = fib::lds_bytes_for(c->threads, c->levels);
-  const bool windowed = c->win.width > 0 && c->d_vmid;
+  const bool windowed = diffuse_windowed(c, true);
   if (windowed) a.v_out = c->d_vmid;
   auto diffuse = [&]() {
     return windowed ? fib::launch_diffuse_window(c->win, c->d_vmid, c->d_state, a, c->stream)
@@ -1842,7 +1879,7 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
   // launches that end a run leave V_m in the state, those a diffusion follows
   // where it reads it
   const KArgs fin = a;
-  if (c->win.width > 0 && c->d_vmid) a.v_out = c->d_vmid;
+  if (diffuse_windowed(c, false)) a.v_out = c->d_vmid;
   if (godunov) {
     // SPLIT, Godunov: per split step one reaction launch (observables of
     // step n-1, then step n's prescriptions and its whole reaction) and one
