@@ -1062,7 +1062,7 @@ int run_adaptive(fib_ctx* c, KArgs a, int64_t step0, int64_t n_steps) {
   if (int rc = adapt_align_flags(c, step0)) return rc;
   const int32_t longest = *std::max_element(c->n_nodes.begin(), c->n_nodes.end());
   if (c->p.model == FIB_MODEL_ST57 && c->win.width > 0 && c->d_first &&
-      fib::adapt_fiber_fits(longest, nt, c->max_lds)) {
+      fib::adapt_fiber_fits(longest, c->n_fibers, nt, c->cu_count, c->max_lds)) {
     // one launch, a fiber per workgroup
     a.pt_prev = c->d_pt + ((step0 + 1) & 1) * nt;
     a.pt_cur = c->d_pt + ((end - 1) & 1) * nt;

@@ -291,7 +291,7 @@ hipError_t launch_diffuse_window(const WindowStencil& st, const float* in, float
 // Adaptive runs of the 57-state model, one fiber per workgroup: whether to
 // take it for a longest fiber of n nodes of nt, and the launch (first: the
 // fibers' first nodes and n_total).
-bool adapt_fiber_fits(int n, int64_t nt, size_t lds);
+bool adapt_fiber_fits(int n, int n_fibers, int64_t nt, int cus, size_t lds);
 hipError_t launch_run_st57_adapt(bool godunov, const WindowStencil& st, const int32_t* first,
                                  int n_fibers, int max_nodes, int cus, const KArgs& a,
                                  hipStream_t s);

@@ -529,21 +529,34 @@ hipError_t launch_diffuse_window(const WindowStencil& st, const float* in, float
   return hipGetLastError();
 }
 
-// A thread's masks hold 32 nodes.  The chip takes 131072 nodes a round, a
-// fiber's workgroup 512, and a round of either is about 40 us a step (two
-// waves per SIMD); the launches cost 65 us, the workgroup 12.  So the
-// workgroup is not behind, with up to half the longest fiber solved, while
-// its rounds are at most one more than the chip's.
-bool adapt_fiber_fits(int n, int64_t nt, size_t lds) {
-  return n <= 32 * 256 && (n + 1023) / 1024 <= 1 + (nt + 131071) / 131072 &&
-         adapt_fiber_lds(n) <= lds;
+// Threads of a fiber's workgroup: with more fibers than compute units two
+// workgroups of four waves share a unit.
+static int adapt_fiber_threads(int n_fibers, int cus) { return n_fibers > cus ? 256 : 512; }
+
+// Whether the longest fiber (n nodes) fits a workgroup (a thread's masks hold 32
+// nodes), and is not behind the launches even with every node solved.  A
+// workgroup then takes its list in rounds of a node per thread, 24 us a step
+// each, 29 where every unit has one; the launches take 30 us a step and 0.52
+// us per 1000 nodes of the chip (us per step, workgroup / launches, a tenth and
+// all nodes solved: 1 x 101 19 19 / 28 28, 1 x 1000 20 48 / 30 33, 1 x 2000 23 93
+// / 31 34, 64 x 2000 24 97 / 42 88, 256 x 1000 22 59 / 56 167, 400 x 1481 33 160
+// / 69 354, 1500 x 2000 110 739 / 238 1637).  Few long fibers keep the launches:
+// as a tenth of them is solved a workgroup would save a third of a step, and
+// lose two steps where all are.
+bool adapt_fiber_fits(int n, int n_fibers, int64_t nt, int cus, size_t lds) {
+  if (n > 32 * 256 || adapt_fiber_lds(n) > lds) return false;
+  const int threads = adapt_fiber_threads(n_fibers, cus), resident = cus * (512 / threads);
+  const double rounds = (double)((n + threads - 1) / threads) *
+                        (double)((n_fibers + resident - 1) / resident);
+  const double busy = n_fibers < cus ? (double)n_fibers / cus : 1.0;
+  return rounds * (24.0 + 5.0 * busy) <= 1.1 * (30.0 + 0.52e-3 * (double)nt);
 }
 
 hipError_t launch_run_st57_adapt(bool godunov, const WindowStencil& st, const int32_t* first,
                                  int n_fibers, int max_nodes, int cus, const KArgs& a,
                                  hipStream_t s) {
   if (a.n_total == 0) return hipSuccess;
-  const dim3 grid((unsigned)n_fibers), block(n_fibers > cus ? 256 : 512);
+  const dim3 grid((unsigned)n_fibers), block((unsigned)adapt_fiber_threads(n_fibers, cus));
   const size_t lds = adapt_fiber_lds(max_nodes);
 #define FIB_LAUNCH(W)                                                                          \
   if (st.width == W) {                                                                         \
