@@ -127,7 +127,8 @@ typedef struct {
   int32_t tune;              /* 0: keep the plan; 1: the first fib_run that advances any
                                 step first runs fib_autotune (100 trial steps, 8
                                 candidates) from the state it is given, which the
-                                autotuner restores, then runs on the chosen plan */
+                                autotuner restores, then runs on the chosen plan (of
+                                whole fibers: such a context never takes windows) */
 } fib_params;
 
 /* One stimulus entry on nodes node-half_width .. node+half_width of fiber
@@ -309,7 +310,10 @@ int fib_plan_info(const fib_t* ctx, int32_t* groups, int32_t* threads, int32_t* 
  * with at most 30 % padding by the slots one SIMD sweeps per step, times
  * the current plan and up to max_candidates - 1 of the best-ranked ones
  * over trial_steps split steps of fib_run from the current state (HIP
- * events on the context's stream), and keeps the fastest.  The state,
+ * events on the context's stream), and keeps the fastest.  Where plain runs
+ * take Hodgkin-Huxley steps on windows, which no shape changes, those are the
+ * first candidate: under AUTO the context stays on them unless a workgroup of
+ * whole fibers is faster, and under SPLIT they are the only one.  The state,
  * activation times and previous-V_m buffers are restored afterwards, so a
  * tuned context continues exactly where it was; results of later runs
  * differ from the untuned plan only by FP32 rounding (the partitioned

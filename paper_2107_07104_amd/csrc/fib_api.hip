@@ -296,7 +296,8 @@ struct fib_ctx {
   float* d_vmid = nullptr;
   float* d_alt = nullptr;
   fib::WindowPlan win_plan{};
-  bool win_auto = false;      // schedule AUTO takes windows, not the fused kernel
+  bool win_auto = false;      // schedule AUTO takes windows, not the fused kernel ...
+  bool win_off = false;       // ... unless the autotuner found that one faster
 
   // surrogate
   bool sur_on = false;
@@ -868,6 +869,14 @@ void window_create(fib_ctx* c) {
     c->win_auto = automatic && cost < waves * c->K * (waves > 1 ? 820.0 : 980.0) + 2100.0;
   }
   if (c->win_auto || c->p.schedule == FIB_SCHED_SPLIT) window_setup(c, true);
+}
+
+// Whether plain runs may take whole steps on windows, whatever the autotuner
+// found: the split schedule always, AUTO where window_create chose them.
+bool windows_apply(const fib_ctx* c) {
+  const bool hh_like = c->p.model == FIB_MODEL_HH || c->p.model == FIB_MODEL_HH_APX_EXP;
+  return hh_like && !c->sur_on && c->win.width > 0 && c->d_alt &&
+         (c->p.schedule == FIB_SCHED_SPLIT || (c->p.schedule == FIB_SCHED_AUTO && c->win_auto));
 }
 
 int check_ctx(const fib_ctx* c) {
@@ -1861,8 +1870,7 @@ int fib_run(fib_t* c, int64_t step0, int64_t n_steps, int64_t sample_every, floa
   const bool hh_like = c->p.model == FIB_MODEL_HH || c->p.model == FIB_MODEL_HH_APX_EXP;
   const bool fused = c->p.schedule == FIB_SCHED_FUSED ||
                      (c->p.schedule == FIB_SCHED_AUTO && hh_like && !c->sur_on);
-  if (hh_like && !c->sur_on && c->win.width > 0 && c->d_alt &&
-      (c->p.schedule == FIB_SCHED_SPLIT || (fused && c->win_auto && !c->tuned)))
+  if (windows_apply(c) && !c->win_off)
     return run_windows(c, a, step0, n_steps, fused ? 0 : graph_period(c, a),
                        fused ? FIB_KT_FUSED : FIB_KT_REACTION);
   if (fused) {
@@ -1947,11 +1955,10 @@ int fib_autotune(fib_t* c, int32_t trial_steps, int32_t max_candidates, double* 
   if (int rc = check_ctx(c)) return rc;
   // the trials time the plain schedule; the adaptive flags stay untouched
   const double tol = c->adapt_tol;
-  const bool tuned = c->tuned;
+  const bool off = c->win_off;
   c->adapt_tol = 0.0;
-  c->tuned = true;  // the shapes are the whole-fiber kernels'
   const int rc = autotune_impl(c, trial_steps, max_candidates, ms_per_step);
-  if (rc) c->tuned = tuned;
+  if (rc) c->win_off = off;
   c->adapt_tol = tol;
   return rc;
 }
@@ -1966,7 +1973,7 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
   // 64) and nodes per thread that hold the heaviest bin with at most 30 %
   // padding, ranked by the slots one SIMD sweeps per step (waves per SIMD x K)
   const int64_t load = max_bin_load(c);
-  struct Cand { int T, K; int64_t cost; };
+  struct Cand { int T, K; int64_t cost; bool windows; };
   std::vector<Cand> cand;
   for (int K = 2; K <= 14; ++K) {
     const int maxT = fib::plan_max_threads(K);
@@ -1974,16 +1981,21 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
       const int64_t capn = (int64_t)T * K;
       if (capn < load || capn * 10 > load * 13) continue;
       if (fib::lds_bytes_for(T, 1) > c->max_lds) continue;
-      cand.push_back({T, K, (int64_t)((T / 64 + 3) / 4) * K});
+      cand.push_back({T, K, (int64_t)((T / 64 + 3) / 4) * K, false});
     }
   }
   std::sort(cand.begin(), cand.end(), [](const Cand& x, const Cand& y) {
     return x.cost != y.cost ? x.cost < y.cost : x.T < y.T;
   });
   std::vector<Cand> trial;
-  trial.push_back({c->threads, c->K, 0});
+  // a context whose runs take whole steps on windows: those first, which no
+  // shape changes; under AUTO then the whole-fiber kernel that may replace them
+  const bool windows = windows_apply(c), only_windows = windows && c->p.schedule == FIB_SCHED_SPLIT;
+  if (windows) trial.push_back({c->threads, c->K, 0, true});
+  if ((int)trial.size() < max_candidates && !only_windows)
+    trial.push_back({c->threads, c->K, 0, false});
   for (const Cand& x : cand) {
-    if ((int)trial.size() >= max_candidates) break;
+    if ((int)trial.size() >= max_candidates || only_windows) break;
     if (x.cost * 100 > cand[0].cost * 112) break;
     if (x.T == c->threads && x.K == c->K) continue;
     trial.push_back(x);
@@ -2027,6 +2039,7 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
     const size_t old = std::max<size_t>(c->slot_gidx.size(), 1);
     c->threads = x.T;
     c->K = x.K;
+    if (windows) c->win_off = !x.windows;
     build_tables(c);
     if (fib::lds_bytes_for(c->threads, c->levels) > c->max_lds) continue;
     if ((rc = upload_plan(c, old))) break;
@@ -2051,6 +2064,8 @@ static int autotune_impl(fib_t* c, int32_t trial_steps, int32_t max_candidates, 
     const size_t old = std::max<size_t>(c->slot_gidx.size(), 1);
     c->threads = pick.T;
     c->K = pick.K;
+    if (windows) c->win_off = !pick.windows;
+    if (!pick.windows) c->tuned = true;
     build_tables(c);
     rc = upload_plan(c, old);
   }
