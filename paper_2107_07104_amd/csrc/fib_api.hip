@@ -242,7 +242,24 @@ int64_t ceil_steps(double span, double dt) {
 // Context
 // ---------------------------------------------------------------------------
 
-struct fib_ctx {
+// Bins, workgroup shape and slot tables of the kernels that take whole fibers,
+// with their device copies.
+struct Plan {
+  int groups = 0, threads = 0, K = 0, cap = 0, levels = 0;
+  uint64_t plan_version = 0;           // differs between any two tables of a context
+  std::vector<int32_t> slot_gidx;      // groups * cap
+  std::vector<uint32_t> slot_base;     // coupling and real-node bits
+  std::vector<std::vector<int32_t>> bin_fibers;
+  // fiber entries of the bins (KArgs::bin_ent and following)
+  std::vector<int32_t> bin_ent, ent_s0, ent_gofs, ent_fiber;
+  int32_t max_ents = 1;
+  int32_t* d_slot_gidx = nullptr;
+  uint32_t* d_slot_info = nullptr;
+  int32_t* d_bin_ent = nullptr;  // bin_ent, then ent_s0, ent_gofs, ent_fiber
+  size_t ent_alloc = 0;          // int32 values in d_bin_ent
+};
+
+struct fib_ctx : Plan {
   fib_params p{};
   int S = 0;
   int32_t n_fibers = 0;
@@ -255,14 +272,13 @@ struct fib_ctx {
   size_t max_lds = 0;
   double rest[fib::MAX_STATES] = {};
 
-  // plan
-  int groups = 0, threads = 0, K = 0, cap = 0, levels = 0;
-  std::vector<int32_t> slot_gidx;      // groups * cap
-  std::vector<uint32_t> slot_base;     // coupling and real-node bits
-  std::vector<std::vector<int32_t>> bin_fibers;
-  // fiber entries of the bins (KArgs::bin_ent and following)
-  std::vector<int32_t> bin_ent, ent_s0, ent_gofs, ent_fiber;
-  int32_t max_ents = 1;
+  // the plan in use is the base; with adapt_planned that is the one chosen for
+  // the adaptive fused kernel and `other` the plain one, without it `other`
+  // holds the adaptive one once there is one (other_ready)
+  Plan other;
+  bool other_ready = false;
+  bool none_fits = false;     // no plan fits the adaptive fused kernel
+  uint64_t plan_count = 0;
   // PCR levels of fib_step_diffusion's last span (for the plan version)
   uint64_t lv_cache_version = ~0ull;
   double lv_cache_r = -1.0;
@@ -273,10 +289,6 @@ struct fib_ctx {
   float* d_tact = nullptr;
   float* d_vprev = nullptr;
   int* d_flag = nullptr;
-  int32_t* d_slot_gidx = nullptr;
-  uint32_t* d_slot_info = nullptr;
-  int32_t* d_bin_ent = nullptr;  // bin_ent, then ent_s0, ent_gofs, ent_fiber
-  size_t ent_alloc = 0;          // int32 values in d_bin_ent
   int32_t* d_node_stim = nullptr;
   fib::StimDev* d_stim = nullptr;
   int32_t n_stim = 0;
@@ -330,7 +342,7 @@ struct fib_ctx {
   uint8_t* d_slot_fiber = nullptr;     // [groups * cap] bin-local fiber of each slot
   int32_t* d_bin_first_on = nullptr;   // [groups * kBinFibers]
   size_t adapt_slots = 0, adapt_bins = 0;  // allocated sizes
-  uint64_t plan_version = 0, stim_version = 0;
+  uint64_t stim_version = 0;
   uint64_t adapt_tables_plan = ~0ull, adapt_tables_stim = ~0ull;
   bool adapt_fused_ok = false;
 
@@ -438,7 +450,8 @@ void pack_bins(fib_ctx* c, int groups) {
 // Reduced-system coefficients (Ra, Rd, Rc) of every thread of one bin in
 // FP64, the same quantities the kernels derive in FP32; used to pick the
 // number of PCR levels after which every remaining coupling is below
-// 2^-40 of its diagonal.
+// 2^-40 of its diagonal.  Most threads hold inner nodes of one fiber only and
+// share one row.
 int pcr_levels_needed(const fib_ctx* c, int bin, double r, bool full) {
   const int T = c->threads, K = c->K;
   const int full_levels = (int)std::ceil(std::log2((double)T) - 1e-12);
@@ -446,11 +459,34 @@ int pcr_levels_needed(const fib_ctx* c, int bin, double r, bool full) {
   std::vector<double> Ra(T), Rd(T), Rc(T), v0(T), w0(T), vL(T), wL(T), ae(T), ce(T), de(T);
   constexpr int KM = 16;  // nodes per thread of any built shape (at most 14)
   if (K > KM) return full_levels;
+  // bit 0: a left neighbour in the fiber, bit 1: a right one
+  std::vector<uint8_t> couple((size_t)T * K, 0);
+  size_t pos = 0;
+  for (int32_t f : c->bin_fibers[bin]) {
+    const size_t n = (size_t)c->n_nodes[f];
+    std::fill(couple.begin() + pos, couple.begin() + pos + n, (uint8_t)3);
+    couple[pos] &= 2;
+    couple[pos + n - 1] &= 1;
+    pos += n;
+  }
+  int inner = -1;  // a thread of inner nodes
   for (int t = 0; t < T; ++t) {
+    const uint8_t* cp_t = couple.data() + (size_t)t * K;
+    const bool is_inner = std::all_of(cp_t, cp_t + K, [](uint8_t x) { return x == 3; });
+    if (is_inner && inner >= 0) {
+      v0[t] = v0[inner];
+      w0[t] = w0[inner];
+      vL[t] = vL[inner];
+      wL[t] = wL[inner];
+      ae[t] = ae[inner];
+      ce[t] = ce[inner];
+      de[t] = de[inner];
+      continue;
+    }
+    if (is_inner) inner = t;
     double a[KM], cc[KM], d[KM];
     for (int q = 0; q < K; ++q) {
-      const uint32_t info = c->slot_base[(size_t)bin * c->cap + (size_t)t * K + q];
-      const bool L = info & fib::SLOT_L, R = info & fib::SLOT_R;
+      const bool L = cp_t[q] & 1, R = cp_t[q] & 2;
       const double wl = L ? (R ? 0.5 * r : r) : 0.0, wr = R ? (L ? 0.5 * r : r) : 0.0;
       a[q] = -wl;
       cc[q] = -wr;
@@ -546,10 +582,17 @@ void set_diffusion(const fib_ctx* c, double dt_cn, KArgs& a) {
   a.rhs = (float)(1.0 / theta_of(c->p));
 }
 
-// Fills the slot tables and the PCR level count of the current shape
-// (groups, threads, K) and bins.
-void build_tables(fib_ctx* c) {
-  ++c->plan_version;
+// PCR levels of the current shape and bins for the matrix of the split step's
+// diffusion substep.
+int split_step_levels(const fib_ctx* c) {
+  const int64_t n_cn = ceil_steps(c->p.dt_split, c->p.dt_1D);
+  return max_pcr_levels(c, 2.0 * theta_of(c->p) * cn_r(c, c->p.dt_split / (double)n_cn));
+}
+
+// Fills the slot tables of the current shape (groups, threads, K) and bins and,
+// where it is not known yet, the PCR level count.
+void build_tables(fib_ctx* c, bool count_levels = true) {
+  c->plan_version = ++c->plan_count;
   c->cap = c->threads * c->K;
   const size_t nslots = (size_t)c->groups * c->cap;
   c->slot_gidx.assign(nslots, -1);
@@ -557,15 +600,16 @@ void build_tables(fib_ctx* c) {
   for (int b = 0; b < c->groups; ++b) {
     size_t pos = (size_t)b * c->cap;
     for (int32_t f : c->bin_fibers[b]) {
-      const int32_t n = c->n_nodes[f];
+      const int32_t n = c->n_nodes[f], first = (int32_t)c->offsets[f];
+      int32_t* gidx = c->slot_gidx.data() + pos;
+      uint32_t* base = c->slot_base.data() + pos;
       for (int32_t j = 0; j < n; ++j) {
-        uint32_t info = fib::SLOT_REAL;
-        if (j > 0) info |= fib::SLOT_L;
-        if (j + 1 < n) info |= fib::SLOT_R;
-        c->slot_gidx[pos] = (int32_t)(c->offsets[f] + j);
-        c->slot_base[pos] = info;
-        ++pos;
+        gidx[j] = first + j;
+        base[j] = fib::SLOT_REAL | fib::SLOT_L | fib::SLOT_R;
       }
+      base[0] &= ~fib::SLOT_L;
+      base[n - 1] &= ~fib::SLOT_R;
+      pos += n;
     }
   }
   c->bin_ent.assign(1, 0);
@@ -587,10 +631,7 @@ void build_tables(fib_ctx* c) {
     c->bin_ent.push_back((int32_t)c->ent_s0.size());
     c->max_ents = std::max<int32_t>(c->max_ents, (int32_t)c->bin_fibers[b].size() + 1);
   }
-  // PCR levels for the matrix of the split step's diffusion substep
-  const int64_t n_cn = ceil_steps(c->p.dt_split, c->p.dt_1D);
-  const double r = 2.0 * theta_of(c->p) * cn_r(c, c->p.dt_split / (double)n_cn);
-  c->levels = max_pcr_levels(c, r);
+  if (count_levels) c->levels = split_step_levels(c);
 }
 
 int64_t max_bin_load(const fib_ctx* c) {
@@ -665,14 +706,21 @@ int make_plan(fib_ctx* c) {
   return FIB_OK;
 }
 
-// Slot-info words with the stimulus entry of each real slot.
-std::vector<uint32_t> slot_info_with_stim(const fib_ctx* c) {
-  std::vector<uint32_t> info(c->slot_base);
-  if (!c->node_stim.empty())
+// Slot-info words of a plan with the stimulus entry of each real slot.
+std::vector<uint32_t> slot_info_with_stim(const fib_ctx* c, const Plan& p) {
+  std::vector<uint32_t> info(p.slot_base);
+  if (c->n_stim > 0)
     for (size_t k = 0; k < info.size(); ++k)
-      if (c->slot_gidx[k] >= 0)
-        info[k] |= (uint32_t)c->node_stim[c->slot_gidx[k]] << fib::SLOT_STIM_SHIFT;
+      if (p.slot_gidx[k] >= 0)
+        info[k] |= (uint32_t)c->node_stim[p.slot_gidx[k]] << fib::SLOT_STIM_SHIFT;
   return info;
+}
+
+void free_plan(Plan& p) {
+  (void)hipFree(p.d_slot_gidx);
+  (void)hipFree(p.d_slot_info);
+  (void)hipFree(p.d_bin_ent);
+  p = Plan{};
 }
 
 // Uploads the slot tables of the current plan (reallocating them if their
@@ -704,7 +752,7 @@ int upload_plan(fib_ctx* c, size_t old_slots) {
     h.insert(h.end(), c->ent_fiber.begin(), c->ent_fiber.end());
     HIP_TRY(hipMemcpy(c->d_bin_ent, h.data(), sizeof(int32_t) * nent, hipMemcpyHostToDevice));
   }
-  const std::vector<uint32_t> info = slot_info_with_stim(c);
+  const std::vector<uint32_t> info = slot_info_with_stim(c, *c);
   if (!c->slot_gidx.empty()) {
     HIP_TRY(hipMemcpy(c->d_slot_gidx, c->slot_gidx.data(), sizeof(int32_t) * c->slot_gidx.size(),
                       hipMemcpyHostToDevice));
@@ -970,33 +1018,36 @@ void fused_shape(int64_t load, Fits fits, int& T, int& K) {
 // need 170 KB), and the split schedule it would fall back to takes three
 // launches per step (1369 fibers, 200 steps: 7.3 ms against 2.4 ms fused).  So
 // the shape, and if no shape of these bins fits, more and smaller bins, are
-// chosen for that kernel; fib_set_adaptive(0) returns to the plain plan.
-// Where nothing fits the plan stays.  The stream must be idle.
+// chosen for that kernel, once per context; turning the adaptive computation
+// on and off then only exchanges the two plans, whose tables both stay on the
+// device (running kernels keep theirs).  Where nothing fits the plan stays.
 int adapt_plan(fib_ctx* c, bool on) {
   const bool automatic = c->p.schedule == FIB_SCHED_AUTO && c->p.model == FIB_MODEL_HH &&
                          c->p.threads_per_group == 0 && c->p.nodes_per_thread == 0 &&
                          c->p.groups == 0 && !c->tuned && c->n_total > 0;
   if (!automatic || on == c->adapt_planned) return FIB_OK;
-  const size_t old = std::max<size_t>(c->slot_gidx.size(), 1);
-  if (!on) {
-    c->adapt_planned = false;
-    if (int rc = make_plan(c)) return rc;
-    return upload_plan(c, old);
+  auto exchange = [&]() { std::swap(static_cast<Plan&>(*c), c->other); };
+  if (!on || c->other_ready) {
+    exchange();
+    c->adapt_planned = on;
+    return FIB_OK;
   }
   auto holds = [&]() {
     for (auto& b : c->bin_fibers)
       if ((int)b.size() > fib::kBinFibers) return false;
     return fib::lds_bytes_for(c->threads, c->levels) + fib::adapt_lds_extra(c->cap) <= c->max_lds;
   };
-  if (holds()) return FIB_OK;
-  for (int groups = c->groups;; groups = std::min(2 * groups, c->n_fibers)) {
-    if (groups != c->groups) {
-      pack_bins(c, groups);
-      c->groups = groups;
-    }
+  if (c->none_fits || holds()) return FIB_OK;
+  Plan next;  // on the plain plan's bins first
+  next.groups = c->groups;
+  next.bin_fibers = c->bin_fibers;
+  c->other = std::move(next);
+  exchange();
+  bool found = false;
+  for (;;) {
     const int64_t load = max_bin_load(c);
     std::vector<std::pair<int, int>> no;  // shapes whose PCR levels take too much LDS
-    for (bool found = true; found && !c->adapt_planned;) {
+    for (;;) {
       int T, K;
       fused_shape(load,
                   [&](int t, int k) {
@@ -1004,21 +1055,31 @@ int adapt_plan(fib_ctx* c, bool on) {
                            std::find(no.begin(), no.end(), std::make_pair(t, k)) == no.end();
                   },
                   T, K);
-      found = K > 0;
-      if (!found) break;
+      if (K == 0) break;
       c->threads = T;
       c->K = K;
-      build_tables(c);
-      c->adapt_planned = holds();
+      c->cap = T * K;
+      c->levels = split_step_levels(c);
+      if ((found = holds())) break;
       no.push_back({T, K});
     }
-    if (c->adapt_planned) break;
-    if (groups >= c->n_fibers) {  // nothing fits: the plain plan again
-      if (int rc = make_plan(c)) return rc;
-      return upload_plan(c, old);
-    }
+    if (found || c->groups >= c->n_fibers) break;
+    c->groups = std::min(2 * c->groups, c->n_fibers);
+    pack_bins(c, c->groups);
   }
-  return upload_plan(c, old);
+  int rc = FIB_OK;
+  if (found) {
+    build_tables(c, false);
+    rc = upload_plan(c, 0);
+  }
+  if (found && !rc) {
+    c->adapt_planned = c->other_ready = true;
+    return FIB_OK;
+  }
+  exchange();  // the plain plan again
+  free_plan(c->other);
+  c->none_fits = !found;
+  return rc;
 }
 
 // The point flags of step step0 - 1 must sit in buffer (step0 - 1) & 1.
@@ -1573,9 +1634,8 @@ void fib_destroy(fib_t* c) {
   (void)hipFree(c->d_tact);
   (void)hipFree(c->d_vprev);
   (void)hipFree(c->d_flag);
-  (void)hipFree(c->d_slot_gidx);
-  (void)hipFree(c->d_slot_info);
-  (void)hipFree(c->d_bin_ent);
+  free_plan(*c);
+  free_plan(c->other);
   (void)hipFree(c->d_node_stim);
   (void)hipFree(c->d_stim);
   (void)hipFree(c->d_ends);
@@ -1714,7 +1774,6 @@ int fib_set_stimulus(fib_t* c, const fib_stim* s, int32_t n) {
     return fail(FIB_EINVAL, "too many stimulus entries");
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->node_stim = node_stim;
-  const std::vector<uint32_t> info = slot_info_with_stim(c);
   (void)hipFree(c->d_stim);
   c->d_stim = nullptr;
   c->n_stim = 0;
@@ -1732,9 +1791,13 @@ int fib_set_stimulus(fib_t* c, const fib_stim* s, int32_t n) {
   if (c->n_total > 0)
     HIP_TRY(hipMemcpy(c->d_node_stim, node_stim.data(), sizeof(int32_t) * c->n_total,
                       hipMemcpyHostToDevice));
-  if (!info.empty())
-    HIP_TRY(hipMemcpy(c->d_slot_info, info.data(), sizeof(uint32_t) * info.size(),
-                      hipMemcpyHostToDevice));
+  for (const Plan* p : {static_cast<const Plan*>(c), static_cast<const Plan*>(&c->other)}) {
+    if (!p->d_slot_info) continue;
+    const std::vector<uint32_t> info = slot_info_with_stim(c, *p);
+    if (!info.empty())
+      HIP_TRY(hipMemcpy(p->d_slot_info, info.data(), sizeof(uint32_t) * info.size(),
+                        hipMemcpyHostToDevice));
+  }
   return FIB_OK;
 }
 
@@ -2298,8 +2361,6 @@ int fib_set_adaptive(fib_t* c, double tol) {
   if (!(std::isfinite(tol) && tol >= 0.0)) return fail(FIB_EINVAL, "tol must be finite and >= 0");
   if (tol == 0.0) {
     c->adapt_tol = 0.0;
-    if (!c->adapt_planned) return FIB_OK;
-    HIP_TRY(hipStreamSynchronize(c->stream));
     return adapt_plan(c, false);
   }
   if (c->sur_on)
