@@ -43,8 +43,8 @@ struct MlpShape {
 // gradients and loss.
 inline int64_t mlp_chunk_floats(const MlpShape& s) { return (int64_t)s.n_ops * 256 + s.n_bias + 1; }
 // Floats of the allocation-free entry point's fixed scratch: the work space
-// of at least 150 chunks whatever the widths (203 chunks of the 57-128-128-57
-// network's).
+// of at least 150 chunks whatever the widths (794 chunks of the 57-128-128-57
+// network's, batches of 25 408).
 constexpr int64_t kScratchFloats = (int64_t)1 << 23;  // 32 MiB per device
 int mlp_pass_chunks(const MlpShape& s, int64_t B);
 

@@ -368,13 +368,16 @@ struct AdamArgs {
   float lr, b1, b2, eps, bc1, bc2;
 };
 
+// Position of a parameter (in < 0: a bias).
+__device__ __forceinline__ int param_index(const MlpShape& s, int l, int out, int in) {
+  return in < 0 ? s.b_off[l] + out : s.w_off[l] + out * s.size[l - 1] + in;
+}
+
 // The gradient of one parameter is ready: grad, and with Adam the FP32
-// master and its BF16 fragments (in < 0: a bias).
+// master and its BF16 fragments.
 __device__ __forceinline__ void finish_param(const MlpShape& s, int l, int out, int in, float acc,
-                                             bool add, float* __restrict__ grad,
-                                             const AdamArgs& ad) {
-  const int p = in < 0 ? s.b_off[l] + out : s.w_off[l] + out * s.size[l - 1] + in;
-  if (add) acc += grad[p];
+                                             float* __restrict__ grad, const AdamArgs& ad) {
+  const int p = param_index(s, l, out, in);
   grad[p] = acc;
   if (!ad.p) return;
   const float mm = fmaf(ad.b1, ad.m[p], (1.0f - ad.b1) * acc);
@@ -398,12 +401,12 @@ constexpr int kAheadChunks = 8;  // chunks of each wave whose operands are in fl
 // chunk and sixteen at a time (one instruction per chunk, K = its 32 samples;
 // eight chunks' operands of every wave in flight), which 256 threads add up in
 // the chunks' order through LDS; the blocks after the tiles sum 64 biases
-// each over the chunks, the last one the loss.  Every sum has one fixed
-// order, over the samples of a chunk and then the chunks, so gradients are
+// each over the chunks, the last one the loss.  Every sum has one
+// fixed order, over the samples of a chunk and then the chunks, so gradients are
 // deterministic and do not depend on how the work is split (Adam's first
 // steps are signs of gradients: an order of its own would send training
-// elsewhere).  add: a later pass of a batch too large for one; the
-// parameters are updated (ad.p non-null) with the last.
+// elsewhere).  add: a later pass of a batch too large for one, which carries
+// the sums on; the parameters are updated (ad.p non-null) with the last.
 //
 // Bound by reading the operands, 2 KB per tile and chunk (64 MB from the
 // last-level cache for a batch of 8192 on the 57-128-128-57 network), and then
@@ -416,7 +419,7 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
     float* __restrict__ loss, AdamArgs ad) {
   __shared__ __align__(16) float sh[2][kUpdWaves][256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, w = threadIdx.x;
-  float sum = 0.0f;  // thread w < 256: element w of the tile
+  float sum = 0.0f;
   if ((int)blockIdx.x < s.n_tiles) {
     int l = 1, tile = blockIdx.x, ib_n;
     for (;; ++l) {
@@ -426,6 +429,10 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
       tile -= nt;
     }
     const int ob = tile / ib_n, ib = tile % ib_n;
+    // thread w < 256: element w of the tile
+    const int out = 16 * ob + 4 * (w >> 6) + (w & 3), in = 16 * ib + ((w >> 2) & 15);
+    const bool mine = w < 256 && out < s.size[l] && in < s.size[l - 1];
+    if (add && mine) sum = grad[param_index(s, l, out, in)];
     const v8bf* pa = ops + (int64_t)(s.d_ops[l] + ob) * 64 + lane;
     const v8bf* pb = ops + (int64_t)(s.a_ops[l] + ib) * 64 + lane;
     const int64_t stride = (int64_t)s.n_ops * 64;
@@ -457,12 +464,13 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
         par ^= 1;
       }
     }
-    if (w >= 256) return;
-    const int out = 16 * ob + 4 * (w >> 6) + (w & 3), in = 16 * ib + ((w >> 2) & 15);
-    if (out < s.size[l] && in < s.size[l - 1]) finish_param(s, l, out, in, sum, add, grad, ad);
+    if (mine) finish_param(s, l, out, in, sum, grad, ad);
     return;
   }
   const int j = ((int)blockIdx.x - s.n_tiles) * 64 + lane;
+  int l = 1;
+  while (l < s.L && j >= s.bias_off[l + 1]) ++l;
+  if (add && j < s.n_bias) sum = grad[param_index(s, l, j - s.bias_off[l], -1)];
   // the waves fetch four chunks each, the first one adds them in order
   for (int c0 = 0; c0 < chunks; c0 += 4 * kUpdWaves) {
 #pragma unroll
@@ -485,10 +493,7 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
     for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
     if (lane == 0) loss[0] = add ? loss[0] + a : a;
   }
-  if (j >= s.n_bias) return;
-  int l = 1;
-  while (l < s.L && j >= s.bias_off[l + 1]) ++l;
-  finish_param(s, l, j - s.bias_off[l], -1, sum, add, grad, ad);
+  if (j < s.n_bias) finish_param(s, l, j - s.bias_off[l], -1, sum, grad, ad);
 }
 
 // ---------------------------------------------------------------------------
