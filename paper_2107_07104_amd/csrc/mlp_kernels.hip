@@ -85,8 +85,8 @@ static NetLds net_lds(const MlpShape& s, bool grad) {
       t.db[b] = o;
       o += 4 * pmax;
     }
-    t.loss = o;
-    o += 4 * kWaves;
+    t.loss = o;  // (doubles: every block before it is a multiple of 8 bytes)
+    o += 8 * kWaves;
   }
   t.total = o;
   return t;
@@ -172,6 +172,26 @@ __device__ __forceinline__ float scan_samples(float v, float carry, int r) {
   return acc;
 }
 
+// v plus the value of another lane (CTRL, ROWS: a DPP move and the rows it
+// writes; 0 elsewhere).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double plus_lane(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, true);
+  return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sum over the wave, in lane 63 (shuffles through LDS took 0.4 us a chunk).
+__device__ __forceinline__ double wave_sum(double v) {
+  v = plus_lane<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
+  v = plus_lane<0x112, 0xf>(v);
+  v = plus_lane<0x114, 0xf>(v);
+  v = plus_lane<0x118, 0xf>(v);
+  v = plus_lane<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
+  return plus_lane<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+
 // Sums of a lane's four features over the chunk's samples (v[0]: the first
 // 16, v[1]: the others) to db[f .. f + 3].
 __device__ __forceinline__ void sum_samples(const v4f (&v)[2], float* db, int f, int lane) {
@@ -219,7 +239,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
   const int nL = s.size[s.L];
   const float scale = 1.0f / ((float)B * (float)nL);
   const int64_t chunks = (B + kChunk - 1) / kChunk;
-  float lsum = 0.0f;
+  double lsum = 0.0;
   for (int64_t chunk = chunk0 + blockIdx.x; chunk < chunks; chunk += gridDim.x) {
     const int64_t s0 = chunk * kChunk;
     // inputs, zero padded: each wave takes four samples
@@ -277,7 +297,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
             for (int j = 0; j < 4; ++j) {
               const float o = v[j] + bj[j];
               const float diff = s0 + n < B && f + j < nout ? o - tj[sb][j] : 0.0f;
-              lsum += diff * diff;
+              lsum += (double)diff * diff;
               d[sb][j] = diff * scale;
             }
             store_operand(d[sb], dst, t.xstride, reinterpret_cast<__bf16*>(lds + t.dt[l & 1]), n, f);
@@ -345,14 +365,14 @@ __global__ __launch_bounds__(64 * kWaves) void k_mlp(MlpShape s, NetLds t,
         __syncthreads();
       }
       // (launched with one chunk per workgroup)
-      for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-      float* sl = reinterpret_cast<float*>(lds + t.loss);
-      if (lane == 0) sl[wave] = lsum;
+      lsum = wave_sum(lsum);
+      double* sl = reinterpret_cast<double*>(lds + t.loss);
+      if (lane == 63) sl[wave] = lsum;
       __syncthreads();
       if (threadIdx.x == 0) {
-        float a = 0.0f;
+        double a = 0.0;
         for (int w = 0; w < kWaves; ++w) a += sl[w];
-        loss_part[blockIdx.x] = 0.5f * a * scale;
+        loss_part[blockIdx.x] = (float)(0.5 * a / ((double)B * nL));
       }
       return;
     }
@@ -401,7 +421,7 @@ constexpr int kAheadChunks = 8;  // chunks of each wave whose operands are in fl
 // chunk and sixteen at a time (one instruction per chunk, K = its 32 samples;
 // eight chunks' operands of every wave in flight), which 256 threads add up in
 // the chunks' order through LDS; the blocks after the tiles sum 64 biases
-// each over the chunks, the last one the loss.  Every sum has one
+// each over the chunks, the last one the loss (in FP64).  Every sum has one
 // fixed order, over the samples of a chunk and then the chunks, so gradients are
 // deterministic and do not depend on how the work is split (Adam's first
 // steps are signs of gradients: an order of its own would send training
@@ -488,10 +508,10 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_mlp_update(
   }
   if (wave > 0) return;
   if (blockIdx.x + 1 == gridDim.x && loss) {
-    float a = 0.0f;
-    for (int c = lane; c < chunks; c += 64) a += loss_part[c];
+    double a = 0.0;
+    for (int c = lane; c < chunks; c += 64) a += (double)loss_part[c];
     for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-    if (lane == 0) loss[0] = add ? loss[0] + a : a;
+    if (lane == 0) loss[0] = (float)(add ? loss[0] + a : a);
   }
   if (j < s.n_bias) finish_param(s, l, j - s.bias_off[l], -1, sum, grad, ad);
 }
