@@ -1176,7 +1176,7 @@ __global__ __launch_bounds__(256, 2) void k_react_stream(KArgs A, int32_t step_a
     }
     if (both) between();
     for (int s = half; s < n_all; ++s) M::heun(u, A.rest, I, A.tau, A.inv_cm);
-    if (n_a == n_all) between();
+    if (n_a > 0 && n_a == n_all) between();  // (without substeps it ran above)
     if (j < nt) stimulus();
     A.v_out[i] = u[0];
     gfloat* row = (gfloat*)(A.state + (nt + i0));
