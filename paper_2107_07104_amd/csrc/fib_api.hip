@@ -1415,11 +1415,19 @@ int run_graph_blocks(fib_ctx* c, const KArgs& a, int64_t n0, int64_t P, int64_t 
 // graphs (split schedule) whole blocks of P steps are one captured graph of an
 // even number of launches.  The last launch writes d_state: where the number
 // of launches comes out odd one more is made, or, for a single step, the state
-// is copied back.
+// is copied back: unless one workgroup holds every node, whose reads are over
+// before it writes (one step of 300 nodes 6.0 us a call, with the copy 7.3).
 int run_windows(fib_ctx* c, const KArgs& a, int64_t step0, int64_t n_steps, int64_t P, int kt) {
   float* buf[2] = {c->d_state, c->d_alt};
   const int S = c->win_plan.steps, width = c->win.width;
   const bool apx = c->p.model == FIB_MODEL_HH_APX_EXP;
+  if (n_steps == 1 && c->n_total + 2 * width <= 1024) {
+    const int threads = (int)(c->n_total + 2 * width + 63) / 64 * 64;
+    const fib::WindowArgs wa{c->d_state, c->d_state, threads - 2 * width, width, 1};
+    KT_LAUNCH(c, kt, fib::launch_window_hh(apx, c->win, wa, fib::WindowPlan{threads, 1},
+                                           (int32_t)step0, a, c->stream));
+    return FIB_OK;
+  }
   int cur = 0;
   // `count` steps from `n` in launches of an even (parity 0), odd (1) or any
   // (-1) number where count allows it
