@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 namespace fib {
@@ -145,6 +146,19 @@ struct KArgs {
                             // row the windowed diffusion reads)
   float rest[MAX_STATES];   // resting state (FP32); device rows hold y_k - rest[k]
 };
+
+// The v_prev of a kernel whose first argument is its KArgs, read from the
+// kernel's argument segment at the place of the call.  An ordinary read of the
+// argument is moved to the kernel's start and held from there, which for a
+// store at the very end costs the adaptive Hodgkin-Huxley kernel scalar
+// registers through all steps (1369 x 1000-1500 nodes, 200 steps: 2247 us
+// without that store, 2262 with an ordinary read, with this as without).
+__device__ __forceinline__ float* late_v_prev() {
+  typedef __attribute__((address_space(4))) const char seg;
+  seg* p = (seg*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(float* __attribute__((address_space(4))) const*)(p + offsetof(KArgs, v_prev));
+}
 
 // Whether entry e is on during split step n: a pulse of `dur` steps from
 // `on`, repeated every `period` steps if > 0.

@@ -427,6 +427,7 @@ __global__ __launch_bounds__(MAXT) void k_run_hh(KArgs A) {
   }
 
   bool bad = false;
+  float* vp = late_v_prev();  // a surrogate step may follow
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const int32_t g = A.slot_gidx[base + q];
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(MAXT) void k_run_hh(KArgs A) {
       A.state[nt + g] = y[q].m;
       A.state[2 * nt + g] = y[q].h;
       A.state[3 * nt + g] = y[q].n;
-      A.v_prev[g] = y[q].V;  // a surrogate step may follow
+      vp[g] = y[q].V;
       bad |= !isfinite(y[q].V) || !isfinite(y[q].m) || !isfinite(y[q].h) || !isfinite(y[q].n);
     }
   }
@@ -748,6 +749,7 @@ __global__ __launch_bounds__(MAXT) void k_run_hh_adapt(KArgs A) {
   }
 
   bool bad = false;
+  float* vp = late_v_prev();
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const int sl = s0 + q;
@@ -759,7 +761,7 @@ __global__ __launch_bounds__(MAXT) void k_run_hh_adapt(KArgs A) {
         A.state[k * nt + g] = v;
         bad |= !isfinite(v);
       }
-      A.v_prev[g] = vcur[q];
+      vp[g] = vcur[q];
       A.pt_cur[g] = ((s_act[sl >> 5] >> (sl & 31)) & 1u) ? PT_ACTIVE : 0;
     }
   }
