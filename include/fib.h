@@ -267,14 +267,17 @@ int fib_run(fib_t* ctx, int64_t step0, int64_t n_steps, int64_t sample_every, fl
  * nodes of every step; it takes plans with at most 64 fibers per bin whose
  * states fit the LDS (fib_run returns FIB_EUNSUPPORTED otherwise).  SPLIT
  * runs, for Hodgkin-Huxley, one start kernel, the diffusion and (Strang) one
- * finish kernel per step; for ST57 a decision kernel that lists the solved
- * nodes, the reaction parts over that list, and the diffusion (the library
- * then holds a list of n_total 32-bit indices on the device, allocated here;
- * FIB_EUNSUPPORTED for more than 2^31 - 1 nodes, FIB_ENOMEM if it does not
- * fit).  AUTO takes the fused variant where it can, else the split
- * schedule.  FIB_EUNSUPPORTED with an attached surrogate.
+ * finish kernel per step; for ST57 all steps in one launch with a fiber per
+ * workgroup where that is not behind even with every node solved, else a
+ * decision kernel that lists the solved nodes, the reaction parts over that
+ * list, and the diffusion (the library holds a list of n_total 32-bit indices
+ * on the device, allocated here; FIB_EUNSUPPORTED for more than 2^31 - 1
+ * nodes, FIB_ENOMEM if it does not fit).  AUTO takes the fused variant where
+ * it can, else the split schedule; where its plan was chosen by the library
+ * and does not fit the fused variant, the first call chooses one that does,
+ * and the context keeps both.  FIB_EUNSUPPORTED with an attached surrogate.
  * fib_autotune times the plain schedule and leaves the points alone.
- * Blocking. */
+ * Blocking, except that turning it off does not wait for the stream. */
 int fib_set_adaptive(fib_t* ctx, double tol);
 
 /* Node-steps whose reaction was solved by adaptive runs since

@@ -3,8 +3,9 @@ form that takes a launch for each part (pcr_full keeps the partitioned solve
 and with it that form), at the edges of the workgroup: fibers just long enough
 for the stencil, lengths around one and two rounds of the workgroup, more
 fibers than the chip has compute units, one fiber past the length the
-workgroup takes; fibers with one stimulus entry and with more than it caches,
-of both kinds; both splittings.
+workgroup takes; fibers with one stimulus entry and with more than it caches
+(currents); both splittings.  Bundles of few fibers that take several rounds of a
+workgroup run the launches in both contexts.
 
 Bounds: the two forms' diffusions differ by FP32 rounding (1e-3 mV allowed
 over an action potential, as between the solves of the plain schedules), which

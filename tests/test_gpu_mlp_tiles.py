@@ -1,7 +1,7 @@
 """The network kernels at the edges of their tiles: widths around 16 and 32
 (the matrix-core tile and the padding), batches of one sample, one chunk of
-32 samples and just beyond, and more chunks than the gradient has rows
-(256 workgroups, so that a workgroup adds several chunks into its row).
+32 samples and just beyond, and 258 chunks, more than the 128 whose operands
+the gradient's contraction has in flight.
 
 Reference: oracle/mlp.py in FP64 on bfloat16-rounded operands, which takes the
 same rounding decisions as the device except where FP32 and FP64
