@@ -581,8 +581,9 @@ int fib_emg_dims(const fib_emg_t* emg, int32_t* nx, int32_t* ny, int32_t* nz);
  * phi_e, with the residual kept at
  * zero mean (the range of the singular Neumann operator) in every
  * iteration, until ||r||_2 <= tol ||b||_2 or max_iter iterations; phi_e is
- * returned to zero mean.  FP32 vectors, FP64 reductions; tolerances down to
- * about 1e-9 are reachable.  iters and rel_res (nullable)
+ * returned to zero mean.  V_m, the right-hand side and phi_e are FP32, the
+ * reductions FP64, and with the transforms the residual and the operator too;
+ * tolerances down to about 1e-9 are reachable.  iters and rel_res (nullable)
  * receive the iterations taken and ||r|| / ||b|| (0 if b = 0).  Blocking. */
 int fib_emg_solve(fib_emg_t* emg, double tol, int32_t max_iter, int32_t* iters,
                   double* rel_res);

@@ -13,7 +13,7 @@
 //
 // A row is applied as sum_{j != t} w_tj (u_j - u_t): K_D u with the diagonal
 // taken as minus the row's off-diagonal weights, which is exact for K_D
-// (its rows sum to zero).  In FP32 this keeps the constant vector an exact
+// (its rows sum to zero).  In any precision this keeps the constant vector an exact
 // null vector of the operator, as it is of K_D, so the projected Neumann
 // system stays consistent and semi-definite.  Applied with the centre weight
 // rounded on its own, the operator's constant mode has an eigenvalue of the
@@ -67,6 +67,7 @@ struct Grid3 {
   int nx, ny, nz;
   float hx, hy, hz;
   int64_t n;
+  double h64[3];  // hx, hy, hz
 };
 
 // Scalars of the solve, in device memory.  slot[k & 1] holds iteration
@@ -102,17 +103,32 @@ __device__ __forceinline__ bool first_thread() {
   return blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
 }
 
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return fma(a, b, c); }
+
 // 1D linear-element stiffness and mass weights of node i (of n, spacing h)
 // towards its neighbours i - 1, i, i + 1; a missing neighbour weighs 0.
-__device__ __forceinline__ void weights_1d(int i, int n, float h, float (&K)[3], float (&M)[3]) {
-  const float lo = i > 0 ? 1.0f : 0.0f, hi = i + 1 < n ? 1.0f : 0.0f;
-  const float ih = 1.0f / h;
+template <class R>
+__device__ __forceinline__ void weights_1d(int i, int n, R h, R (&K)[3], R (&M)[3]) {
+  const R lo = i > 0 ? R(1) : R(0), hi = i + 1 < n ? R(1) : R(0);
+  const R ih = R(1) / h;
   K[0] = -lo * ih;
   K[1] = (lo + hi) * ih;
   K[2] = -hi * ih;
-  M[0] = lo * h * (1.0f / 6.0f);
-  M[1] = (lo + hi) * h * (1.0f / 3.0f);
-  M[2] = hi * h * (1.0f / 6.0f);
+  M[0] = lo * h * R(1.0 / 6.0);
+  M[1] = (lo + hi) * h * R(1.0 / 3.0);
+  M[2] = hi * h * R(1.0 / 6.0);
+}
+
+template <class R>
+__device__ __forceinline__ R spacing(const Grid3& g, int axis);
+template <>
+__device__ __forceinline__ float spacing<float>(const Grid3& g, int axis) {
+  return axis == 0 ? g.hx : axis == 1 ? g.hy : g.hz;
+}
+template <>
+__device__ __forceinline__ double spacing<double>(const Grid3& g, int axis) {
+  return g.h64[axis];
 }
 
 // Row (i, j, k) of K_D applied to a field u in the difference form
@@ -124,42 +140,47 @@ __device__ __forceinline__ void weights_1d(int i, int n, float h, float (&K)[3],
 // zero).  get(kk, l) returns u at layer kk and in-layer index l = j' nx + i'.
 // A missing neighbour has 1D weight 0, and its offset is clamped to the node
 // itself so that every read stays in the mesh.  diag receives the diagonal
-// weight of K_D (the Jacobi preconditioner).
-template <class Get>
-__device__ __forceinline__ float apply_row(const Grid3& g, float dx, float dy, float dz, int i,
-                                           int j, int k, Get get, float& diag) {
-  float Kx[3], Mx[3], Ky[3], My[3], Kz[3], Mz[3];
-  weights_1d(i, g.nx, g.hx, Kx, Mx);
-  weights_1d(j, g.ny, g.hy, Ky, My);
-  weights_1d(k, g.nz, g.hz, Kz, Mz);
+// weight of K_D (the Jacobi preconditioner).  R: the arithmetic (float, or
+// double on the same FP32 field).  Z: only the last term (dx = dy = 0).
+template <class R, bool Z = false, class Get>
+__device__ __forceinline__ R apply_row(const Grid3& g, R dx, R dy, R dz, int i, int j, int k,
+                                       Get get, R& diag) {
+  R Kx[3], Mx[3], Ky[3], My[3], Kz[3], Mz[3];
+  weights_1d<R>(i, g.nx, spacing<R>(g, 0), Kx, Mx);
+  weights_1d<R>(j, g.ny, spacing<R>(g, 1), Ky, My);
+  weights_1d<R>(k, g.nz, spacing<R>(g, 2), Kz, Mz);
   diag = dx * Kx[1] * My[1] * Mz[1] + dy * Mx[1] * Ky[1] * Mz[1] + dz * Mx[1] * My[1] * Kz[1];
   const uint32_t l0 = (uint32_t)(j * g.nx + i);
   const uint32_t ox[3] = {i > 0 ? ~0u : 0u, 0u, i + 1 < g.nx ? 1u : 0u};
   const uint32_t oy[3] = {j > 0 ? 0u - (uint32_t)g.nx : 0u, 0u, j + 1 < g.ny ? (uint32_t)g.nx : 0u};
   const uint32_t kz[3] = {(uint32_t)(k > 0 ? k - 1 : k), (uint32_t)k,
                           (uint32_t)(k + 1 < g.nz ? k + 1 : k)};
-  const float uc = get((uint32_t)k, l0);
-  float s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+  const R uc = (R)get((uint32_t)k, l0);
+  R s1 = 0, s2 = 0, s3 = 0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    float y1 = 0.0f, y2 = 0.0f, y3 = 0.0f;
+    R y1 = 0, y2 = 0, y3 = 0;
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       const uint32_t l = l0 + oy[b];
-      const float d0 = get(kz[c], l + ox[0]) - uc;
-      const float d1 = get(kz[c], l) - uc;
-      const float d2 = get(kz[c], l + ox[2]) - uc;
-      const float sk = fmaf(Kx[0], d0, fmaf(Kx[1], d1, Kx[2] * d2));
-      const float sm = fmaf(Mx[0], d0, fmaf(Mx[1], d1, Mx[2] * d2));
-      y1 = fmaf(My[b], sk, y1);
-      y2 = fmaf(Ky[b], sm, y2);
-      y3 = fmaf(My[b], sm, y3);
+      const R d0 = (R)get(kz[c], l + ox[0]) - uc;
+      const R d1 = (R)get(kz[c], l) - uc;
+      const R d2 = (R)get(kz[c], l + ox[2]) - uc;
+      const R sk = Z ? R(0) : fma_of(Kx[0], d0, fma_of(Kx[1], d1, Kx[2] * d2));
+      const R sm = fma_of(Mx[0], d0, fma_of(Mx[1], d1, Mx[2] * d2));
+      if (!Z) {
+        y1 = fma_of(My[b], sk, y1);
+        y2 = fma_of(Ky[b], sm, y2);
+      }
+      y3 = fma_of(My[b], sm, y3);
     }
-    s1 = fmaf(Mz[c], y1, s1);
-    s2 = fmaf(Mz[c], y2, s2);
-    s3 = fmaf(Kz[c], y3, s3);
+    if (!Z) {
+      s1 = fma_of(Mz[c], y1, s1);
+      s2 = fma_of(Mz[c], y2, s2);
+    }
+    s3 = fma_of(Kz[c], y3, s3);
   }
-  return fmaf(dx, s1, fmaf(dy, s2, dz * s3));
+  return Z ? dz * s3 : fma_of(dx, s1, fma_of(dy, s2, dz * s3));
 }
 
 // Node of this thread in the (blocks per layer, layers) grid; false past
@@ -257,9 +278,10 @@ __device__ __forceinline__ void total_sums(const double* partials, int nblocks, 
 }
 
 // b = -K_{sigma_i} P V_m from the fiber state (row 0: V_m - rest; the
-// difference form sees only differences of V_m); per-block sums of b.
+// difference form sees only differences of V_m), formed in FP64 and rounded
+// once; per-block sums of b.
 __global__ __launch_bounds__(kB) void k_emg_rhs(Grid3 g, const float* __restrict__ vm,
-                                                int32_t n_fib, int32_t m, float sigma_i,
+                                                int32_t n_fib, int32_t m, double sigma_i,
                                                 float* __restrict__ b, double* partials) {
   int i, j, k;
   uint32_t t;
@@ -269,8 +291,8 @@ __global__ __launch_bounds__(kB) void k_emg_rhs(Grid3 g, const float* __restrict
     auto get = [&](uint32_t kk, uint32_t f) {
       return at(vm, f * (uint32_t)n_fib + kk * (uint32_t)m);
     };
-    float d;
-    const float val = -apply_row(g, 0.0f, 0.0f, sigma_i, i, j, k, get, d);
+    double d;
+    const float val = (float)-apply_row<double, true>(g, 0.0, 0.0, sigma_i, i, j, k, get, d);
     b[t] = val;
     v[0] = val;
   }
@@ -292,9 +314,9 @@ __global__ __launch_bounds__(kB) void k_emg_invd(Grid3 g, float dx, float dy, fl
   double v[1] = {0.0};
   if (node_of(g, i, j, k, t)) {
     float Kx[3], Mx[3], Ky[3], My[3], Kz[3], Mz[3];
-    weights_1d(i, g.nx, g.hx, Kx, Mx);
-    weights_1d(j, g.ny, g.hy, Ky, My);
-    weights_1d(k, g.nz, g.hz, Kz, Mz);
+    weights_1d<float>(i, g.nx, g.hx, Kx, Mx);
+    weights_1d<float>(j, g.ny, g.hy, Ky, My);
+    weights_1d<float>(k, g.nz, g.hz, Kz, Mz);
     const float d = dx * Kx[1] * My[1] * Mz[1] + dy * Mx[1] * Ky[1] * Mz[1] +
                     dz * Mx[1] * My[1] * Kz[1];
     const float w = 1.0f / d;
@@ -332,7 +354,8 @@ __global__ __launch_bounds__(kB) void k_emg_start(Grid3 g, float dx, float dy, f
   double v[4] = {0.0, 0.0, 0.0, 0.0}, vb[1] = {0.0};
   if (node_of(g, i, j, k, t)) {
     float d;
-    const float ax = apply_row(g, dx, dy, dz, i, j, k, MeshVec{x, (uint32_t)(g.nx * g.ny)}, d);
+    const float ax =
+        apply_row<float>(g, dx, dy, dz, i, j, k, MeshVec{x, (uint32_t)(g.nx * g.ny)}, d);
     const float bp = b[t] - (float)s->mean_b;
     const float rt = bp - ax;
     r[t] = rt;
@@ -394,7 +417,7 @@ __global__ __launch_bounds__(kB) void k_cg_q(Grid3 g, float dx, float dy, float 
       return fmaf(beta, at(p_old, n), (at(r, n) - c) * at(invd, n));
     };
     float d;
-    const float qt = apply_row(g, dx, dy, dz, i, j, k, pn, d);
+    const float qt = apply_row<float>(g, dx, dy, dz, i, j, k, pn, d);
     const float pt = fmaf(beta, p_old[t], (r[t] - c) * invd[t]);
     p_new[t] = pt;
     q[t] = qt;
@@ -442,11 +465,17 @@ __global__ __launch_bounds__(kB) void k_cg_x(Grid3 g, const float* __restrict__ 
 // diagonalization of tensor-product operators, Lynch, Rice and Thomas 1964),
 // and its inverse is a cosine transform along each axis, a division and the
 // same transforms back (V is symmetric).  In exact arithmetic the first
-// iteration solves the system; in FP32 rounding of p, amplified by the
-// operator, leaves three digits or so of the residual, and two iterations
-// reach 1e-9 where the diagonal preconditioner took 230 to 1e-7 on 37 x 37 x
-// 149 nodes (14.4 us each, 3.5 ms a solve; now 0.2 ms).  An iteration is five
-// launches:
+// iteration solves the system; with z and p in FP32 the second takes the
+// residual to 1e-11 where the diagonal preconditioner took 230 to 1e-7 on 37 x
+// 37 x 149 nodes (14.4 us each, 3.5 ms a solve; now 0.25 ms).
+//
+// The residual r, q = A p and the rows' arithmetic are FP64 (of FP32 fields p,
+// x and V_m): two iterations average no rounding away, and with r, q and the
+// rows in FP32 what the operator's largest terms rounded off stood in the
+// smooth modes of phi_e (relative error 8e-7 on 6 x 5 x 48 nodes, 8.2e-7 on
+// 37 x 37 x 149; now 1.1e-7 and 5.6e-8).  It costs 8 us of 231 a solve there:
+// the right-hand side 17.0 -> 20.1, k_fdm_xy 9.1 -> 11.2, k_pcg_q 6.9 -> 7.4 us.
+// An iteration is five launches:
 //   k_fdm_xy:   the residual test, then the x and y transforms of one layer;
 //   k_fdm_z:    z transform, division, z transform back, 16 columns;
 //   k_fdm_back: x and y back to z = A^+ r, per-block sums of r.z and z;
@@ -456,7 +485,7 @@ __global__ __launch_bounds__(kB) void k_cg_x(Grid3 g, const float* __restrict__ 
 // The transforms are matrix products on the matrix cores in FP32
 // (v_mfma_f32_16x16x4_f32): 4 (nx + ny + nz) operations per node, 182 MFLOP on
 // 37 x 37 x 149 nodes, so an iteration is bound by its launches and their
-// load latencies (7.6, 10, 6.3, 5.2 and 4.8 us there).
+// load latencies (11.2, 14.5, 8.2, 7.4 and 6.1 us there under the tracer).
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -519,9 +548,9 @@ __device__ __forceinline__ v4f mma_f32(FA a, FB b, int k_n, int lane) {
 // The x and y transforms of one layer U (ny x nx): out = Vy U Vx, through an
 // LDS plane T = U Vx of y.np rows of x.np + 1.  Every wave takes 16 x 16
 // tiles.  put(j, i, v) receives the results inside the layer.
-template <class Put>
+template <class U, class Put>
 __device__ __forceinline__ void plane_transform(const Axis& X, const Axis& Y,
-                                                const float* __restrict__ U, float* T, Put put) {
+                                                const U* __restrict__ in, float* T, Put put) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   const int xt = X.np >> 4, yt = Y.np >> 4, ts = X.np + 1;
   const int r = lane & 15, g = lane >> 4;
@@ -529,7 +558,7 @@ __device__ __forceinline__ void plane_transform(const Axis& X, const Axis& Y,
     const int jb = 16 * (t / xt), ib = 16 * (t % xt);
     const v4f v = mma_f32(
         [&](int m, int k) {
-          return jb + m < Y.n && k < X.n ? U[(jb + m) * X.n + k] : 0.0f;
+          return jb + m < Y.n && k < X.n ? (float)in[(jb + m) * X.n + k] : 0.0f;
         },
         [&](int k, int c) { return k < X.np ? X.V[k * X.np + ib + c] : 0.0f; }, X.n, lane);
 #pragma unroll
@@ -552,7 +581,7 @@ __device__ __forceinline__ void plane_transform(const Axis& X, const Axis& Y,
 // Iteration k (parity P): the test from the sums of r in part_r, then u = the
 // x and y transforms of r, one layer per block (its constant mode, which c
 // belongs to, is dropped by k_fdm_z).
-__global__ __launch_bounds__(1024) void k_fdm_xy(Fdm f, const float* __restrict__ r,
+__global__ __launch_bounds__(1024) void k_fdm_xy(Fdm f, const double* __restrict__ r,
                                                  float* __restrict__ u, const double* part_r,
                                                  int nblocks, int64_t n, int P, Scal* s) {
   extern __shared__ float plane[];
@@ -631,7 +660,7 @@ __global__ __launch_bounds__(1024) void k_fdm_z(Fdm f, float* __restrict__ u, in
 // z = the x and y transforms of u back, one layer per block; per-block sums
 // of r z and z into part_z.
 __global__ __launch_bounds__(1024) void k_fdm_back(Fdm f, const float* __restrict__ u,
-                                                   const float* __restrict__ r,
+                                                   const double* __restrict__ r,
                                                    float* __restrict__ z, double* part_z,
                                                    const Scal* s) {
   extern __shared__ float plane[];
@@ -642,7 +671,7 @@ __global__ __launch_bounds__(1024) void k_fdm_back(Fdm f, const float* __restric
   plane_transform(f.x, f.y, u + base, plane, [&](int j, int i, float zv) {
     const int64_t t = base + j * f.x.n + i;
     z[t] = zv;
-    v[0] += (double)r[t] * zv;
+    v[0] += r[t] * zv;
     v[1] += (double)zv;
   });
 #pragma unroll
@@ -661,10 +690,10 @@ __global__ __launch_bounds__(1024) void k_fdm_back(Fdm f, const float* __restric
 
 // Iteration k (parity P): beta from the sums of r z and z, p_new = z + beta
 // p_old and q = A p_new; per-block sums of p.q into part_pq.
-__global__ __launch_bounds__(kB) void k_pcg_q(Grid3 g, float dx, float dy, float dz,
+__global__ __launch_bounds__(kB) void k_pcg_q(Grid3 g, double dx, double dy, double dz,
                                               const float* __restrict__ z,
                                               const float* __restrict__ p_old,
-                                              float* __restrict__ p_new, float* __restrict__ q,
+                                              float* __restrict__ p_new, double* __restrict__ q,
                                               const double* part_z, double* part_pq, int P,
                                               Scal* s) {
   if (s->done) return;
@@ -686,12 +715,12 @@ __global__ __launch_bounds__(kB) void k_pcg_q(Grid3 g, float dx, float dy, float
       const uint32_t n = kk * nxy + l;
       return fmaf(beta, at(p_old, n), at(z, n));
     };
-    float d;
-    const float qt = apply_row(g, dx, dy, dz, i, j, k, pn, d);
+    double d;
+    const double qt = apply_row<double>(g, dx, dy, dz, i, j, k, pn, d);
     const float pt = fmaf(beta, p_old[t], z[t]);
     p_new[t] = pt;
     q[t] = qt;
-    v[0] = (double)pt * qt;
+    v[0] = pt * qt;
   }
   block_sums<1>(v, part_pq);
 }
@@ -700,25 +729,25 @@ __global__ __launch_bounds__(kB) void k_pcg_q(Grid3 g, float dx, float dy, float
 // c) - alpha q; per-block sums of r and r^2 into part_r (the buffer of parity
 // P ^ 1) and of x into part_x.
 __global__ __launch_bounds__(kB) void k_pcg_x(Grid3 g, const float* __restrict__ p,
-                                              const float* __restrict__ q, float* __restrict__ x,
-                                              float* __restrict__ r, const double* part_pq,
+                                              const double* __restrict__ q, float* __restrict__ x,
+                                              double* __restrict__ r, const double* part_pq,
                                               double* part_r, double* part_x, int nblocks, int P,
                                               const Scal* s) {
   if (s->done) return;
   double tot[1];
   total_sums<1>(part_pq, nblocks, tot);
   const float alpha = tot[0] > 0.0 ? (float)(s->slot[P].rz / tot[0]) : 0.0f;
-  const float c = (float)s->slot[P].c;
+  const double c = s->slot[P].c;
   int i, j, k;
   uint32_t t;
   double v[2] = {0.0, 0.0}, vx[1] = {0.0};
   if (node_of(g, i, j, k, t)) {
     const float xt = fmaf(alpha, p[t], x[t]);
     x[t] = xt;
-    const float rt = fmaf(-alpha, q[t], r[t] - c);
+    const double rt = fma(-(double)alpha, q[t], r[t] - c);
     r[t] = rt;
-    v[0] = (double)rt;
-    v[1] = (double)rt * rt;
+    v[0] = rt;
+    v[1] = rt * rt;
     vx[0] = (double)xt;
   }
   block_sums<2>(v, part_r);
@@ -727,23 +756,24 @@ __global__ __launch_bounds__(kB) void k_pcg_x(Grid3 g, const float* __restrict__
 
 // Start from the last solution x: bp = b - mean(b), r = bp - A x; per-block
 // sums of r and r^2 into part_r, of bp.bp and of x.
-__global__ __launch_bounds__(kB) void k_pcg_start(Grid3 g, float dx, float dy, float dz,
+__global__ __launch_bounds__(kB) void k_pcg_start(Grid3 g, double dx, double dy, double dz,
                                                   const float* __restrict__ b,
                                                   const float* __restrict__ x,
-                                                  float* __restrict__ r, double* part_r,
+                                                  double* __restrict__ r, double* part_r,
                                                   double* part_b, double* part_x, const Scal* s) {
   int i, j, k;
   uint32_t t;
   double v[2] = {0.0, 0.0}, vb[1] = {0.0}, vx[1] = {0.0};
   if (node_of(g, i, j, k, t)) {
-    float d;
-    const float ax = apply_row(g, dx, dy, dz, i, j, k, MeshVec{x, (uint32_t)(g.nx * g.ny)}, d);
-    const float bp = b[t] - (float)s->mean_b;
-    const float rt = bp - ax;
+    double d;
+    const double ax =
+        apply_row<double>(g, dx, dy, dz, i, j, k, MeshVec{x, (uint32_t)(g.nx * g.ny)}, d);
+    const double bp = (double)b[t] - s->mean_b;
+    const double rt = bp - ax;
     r[t] = rt;
-    v[0] = (double)rt;
-    v[1] = (double)rt * rt;
-    vb[0] = (double)bp * bp;
+    v[0] = rt;
+    v[1] = rt * rt;
+    vb[0] = bp * bp;
     vx[0] = (double)x[t];
   }
   block_sums<2>(v, part_r);
@@ -840,7 +870,7 @@ struct fib_emg {
   fib_emg_params p{};
   Grid3 g{};
   int32_t n_fib = 0;          // nodes per fiber
-  float* d_vec = nullptr;     // b, x, r, 1/diag (z), p0, p1, q (and u) (n each)
+  float* d_vec = nullptr;     // b, x, r, 1/diag, p0, p1, q (n each)
   double* d_part = nullptr;   // per-block sums, 9 x blocks
   Scal* d_s = nullptr;
   Scal* h_s = nullptr;        // pinned copy of the scalars
@@ -854,13 +884,16 @@ struct fib_emg {
   float* q() const { return d_vec + 6 * g.n; }
   double* part_r(int par) const { return d_part + (size_t)par * 4 * nblocks; }
   double* part_pq() const { return d_part + (size_t)8 * nblocks; }
-  // the preconditioned solve: transforms of the axes in one array, and its
-  // sums (r in two buffers, p.q, x, b.b, then r.z and z by layer)
+  // the preconditioned solve: transforms of the axes in one array, its vectors
+  // (b, x, u, z, p0, p1, then r and q in FP64), and its sums (r in two buffers,
+  // p.q, x, b.b, then r.z and z by layer)
   bool fdm = false;
   Fdm f{};
   float* d_axes = nullptr;
-  float* u() const { return d_vec + 7 * g.n; }
+  float* u() const { return d_vec + 2 * g.n; }
   float* z() const { return d_vec + 3 * g.n; }
+  double* r64() const { return reinterpret_cast<double*>(d_vec + 6 * g.n); }
+  double* q64() const { return reinterpret_cast<double*>(d_vec + 8 * g.n); }
   double* pcg_r(int par) const { return d_part + (size_t)par * 2 * nblocks; }
   double* pcg_pq() const { return d_part + (size_t)4 * nblocks; }
   double* pcg_x() const { return d_part + (size_t)5 * nblocks; }
@@ -904,6 +937,7 @@ int fdm_solve(fib_emg* e, const fib::CtxView& v, double tol, int32_t max_iter) {
   const Fdm f = e->f;
   const dim3 grid = e->grid, block(kB), one(1);
   const int nb = e->nblocks, cols = g.nx * g.ny;
+  const double dx = e->p.sigma_et, dy = e->p.sigma_et, dz = e->p.sigma_el + e->p.sigma_i;
   // a wave per 16 x 16 tile of a layer (at least the block total_sums wants)
   // and per 16 layers of a panel
   const int tiles = (f.x.np >> 4) * (f.y.np >> 4);
@@ -913,9 +947,9 @@ int fdm_solve(fib_emg* e, const fib::CtxView& v, double tol, int32_t max_iter) {
   const size_t panel = sizeof(float) * f.z.np * 17;
   const int two = 2 * panel <= 128 * 1024;
   hipLaunchKernelGGL(k_emg_rhs, grid, block, 0, st, g, v.d_state, e->n_fib, e->p.stride,
-                     (float)e->p.sigma_i, e->b(), e->d_part);
+                     e->p.sigma_i, e->b(), e->d_part);
   hipLaunchKernelGGL(k_emg_mean, one, block, 0, st, e->d_part, nb, g.n, e->d_s);
-  hipLaunchKernelGGL(k_pcg_start, grid, block, 0, st, g, f.dx, f.dy, f.dz, e->b(), e->x(), e->r(),
+  hipLaunchKernelGGL(k_pcg_start, grid, block, 0, st, g, dx, dy, dz, e->b(), e->x(), e->r64(),
                      e->pcg_r(0), e->pcg_b(), e->pcg_x(), e->d_s);
   hipLaunchKernelGGL(k_pcg_started, one, block, 0, st, e->pcg_r(0), e->pcg_b(), nb, g.n,
                      tol * tol, e->d_s);
@@ -930,15 +964,15 @@ int fdm_solve(fib_emg* e, const fib::CtxView& v, double tol, int32_t max_iter) {
     const int n_it = std::min(batch, max_iter - launched);
     for (int b = 0; b < n_it; ++b) {
       const int P = (launched + b) & 1;
-      hipLaunchKernelGGL(k_fdm_xy, dim3((unsigned)g.nz), bxy, lds_xy, st, f, e->r(), e->u(),
+      hipLaunchKernelGGL(k_fdm_xy, dim3((unsigned)g.nz), bxy, lds_xy, st, f, e->r64(), e->u(),
                          e->pcg_r(P), nb, g.n, P, e->d_s);
       hipLaunchKernelGGL(k_fdm_z, dim3((unsigned)((cols + 15) / 16)), bz,
                          two ? 2 * panel : panel, st, f, e->u(), cols, two, e->d_s);
-      hipLaunchKernelGGL(k_fdm_back, dim3((unsigned)g.nz), bxy, lds_xy, st, f, e->u(), e->r(),
+      hipLaunchKernelGGL(k_fdm_back, dim3((unsigned)g.nz), bxy, lds_xy, st, f, e->u(), e->r64(),
                          e->z(), e->pcg_z(), e->d_s);
-      hipLaunchKernelGGL(k_pcg_q, grid, block, 0, st, g, f.dx, f.dy, f.dz, e->z(), e->pb(P),
-                         e->pb(P ^ 1), e->q(), e->pcg_z(), e->pcg_pq(), P, e->d_s);
-      hipLaunchKernelGGL(k_pcg_x, grid, block, 0, st, g, e->pb(P ^ 1), e->q(), e->x(), e->r(),
+      hipLaunchKernelGGL(k_pcg_q, grid, block, 0, st, g, dx, dy, dz, e->z(), e->pb(P),
+                         e->pb(P ^ 1), e->q64(), e->pcg_z(), e->pcg_pq(), P, e->d_s);
+      hipLaunchKernelGGL(k_pcg_x, grid, block, 0, st, g, e->pb(P ^ 1), e->q64(), e->x(), e->r64(),
                          e->pcg_pq(), e->pcg_r(P ^ 1), e->pcg_x(), nb, P, e->d_s);
     }
     launched += n_it;
@@ -996,6 +1030,9 @@ int fib_emg_create(fib_t* ctx, const fib_emg_params* p, fib_emg_t** out) {
   e->g.hx = (float)p->hx;
   e->g.hy = (float)p->hy;
   e->g.hz = (float)(p->stride * v.h);
+  e->g.h64[0] = p->hx;
+  e->g.h64[1] = p->hy;
+  e->g.h64[2] = p->stride * v.h;
   e->g.n = (int64_t)e->g.nx * e->g.ny * e->g.nz;
   e->grid = dim3((unsigned)((e->g.nx * e->g.ny + kB - 1) / kB), (unsigned)e->g.nz);
   e->nblocks = (int)(e->grid.x * e->grid.y);
@@ -1003,7 +1040,7 @@ int fib_emg_create(fib_t* ctx, const fib_emg_params* p, fib_emg_t** out) {
   // beyond that take the diagonal preconditioner (230 iterations instead of
   // two at 37 x 37 x 149 nodes, and growing with the layers).
   e->fdm = p->nx <= kFdmPlane && p->ny <= kFdmPlane && e->g.nz <= kFdmLayers;
-  const size_t nv = (size_t)e->g.n * (e->fdm ? 8 : 7);
+  const size_t nv = (size_t)e->g.n * (e->fdm ? 10 : 7);
   if (hipMalloc(&e->d_vec, sizeof(float) * nv) != hipSuccess ||
       hipMalloc(&e->d_part, sizeof(double) * 9 * e->nblocks) != hipSuccess ||
       hipMalloc(&e->d_s, sizeof(Scal)) != hipSuccess ||
@@ -1077,7 +1114,7 @@ int fib_emg_solve(fib_emg_t* e, double tol, int32_t max_iter, int32_t* iters, do
   e->h_s->tol2 = tol * tol;
   EHIP(hipMemcpyAsync(&e->d_s->tol2, &e->h_s->tol2, sizeof(double), hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_emg_rhs, grid, block, 0, st, g, v.d_state, e->n_fib, e->p.stride,
-                     (float)e->p.sigma_i, e->b(), e->d_part);
+                     e->p.sigma_i, e->b(), e->d_part);
   hipLaunchKernelGGL(k_emg_mean, one, block, 0, st, e->d_part, nb, g.n, e->d_s);
   hipLaunchKernelGGL(k_emg_start, grid, block, 0, st, g, dx, dy, dz, e->b(), e->x(),
                      e->invd(), e->r(), e->part_r(0), e->part_pq(), e->d_s);
