@@ -138,11 +138,11 @@ ST57_REACT_OPS = 6 * ST57_HEUN_OPS
 # whole node-step: reaction + Crank-Nicolson 11 + activation test 2
 ST57_OPS_PER_NODE_STEP = ST57_REACT_OPS + 13
 
-# EMG conjugate-gradient iteration, per mesh node (FP32 vectors): the
-# transforms read r and write u (8 B), read and write u (8 B), read u and r
-# and write z (12 B); the stencil launch reads z, p_old and writes p, q (16 B);
-# the update launch reads p, q, x, r and writes x, r (24 B)
-EMG_BYTES_PER_NODE_ITERATION = 68
+# EMG conjugate-gradient iteration, per mesh node (FP32 vectors, but r and q
+# FP64): the transforms read r and write u (12 B), read and write u (8 B), read
+# u and r and write z (16 B); the stencil launch reads z, p_old and writes p, q
+# (20 B); the update launch reads p, q, x, r and writes x, r (36 B)
+EMG_BYTES_PER_NODE_ITERATION = 92
 
 HBM_PEAK = 8.0e12
 MFMA_BF16_PEAK = 2.5e15
